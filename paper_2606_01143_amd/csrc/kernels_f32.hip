@@ -1,348 +1,694 @@
-// fp32 storage path: plain vector-ALU kernels, one thread per query row or
-// per key.  On MI355X the fp32 matrix-core peak equals the fp32 vector peak
-// (157.3 TFLOP/s), so fp32 gains nothing from MFMA; this path exists for
-// full-precision parity and is fully deterministic (dQ comes from its own
-// query-outer kernel, no atomics).
+// fp32 storage path on gfx950's fp32 matrix instruction
+// (v_mfma_f32_16x16x4_f32: exact fp32 products and sums, 256 flop per clock
+// and CU, the rate of the vector ALU at its best).  Every product is held
+// and accumulated in fp32, there are no atomics, and every output is bitwise
+// reproducible.
 //
 // Paper equations: forward H = softmax(S) V with the causal mask (App. A.1);
 // backward dV = P^T dO, dP = dO V^T, dS = P * (dP - rowsum(dP * P)),
 // dQ = dS K / sqrt(d), dK = dS^T Q / sqrt(d) (App. A.2-A.4), evaluated per
 // segment tile so prefix and suffix keys are read in place.
+//
+// What bounds it: the matrix instruction, 32 cycles for a 16 x 16 x 4 block.
+// One 16-byte LDS read feeds four of them and one 4-byte read feeds one, so
+// LDS and the vector ALU stay far below their rates and the kernels only
+// need enough waves to cover latency: two workgroups of four waves per CU,
+// 64 KB of double-buffered 32-row tiles each.  16-wide blocks (instead of
+// 32 x 32 x 2) halve the registers a row or key costs, so a small group
+// still spreads over the chip.  Measured on 32/8 heads, d = 128, P = 1000 and
+// four ragged suffixes, per pass: one thread per row or key on the vector ALU
+// 72.1 ms (0.9 TFLOP/s), this form 1.18 ms (56 TFLOP/s useful; the recompute of
+// S and dP for dQ puts 1.3 times that through the matrix cores).
+//
+// v_mfma_f32_16x16x4_f32 operands (lane l, n = l % 16, g = l / 16):
+//   A (16 x 4): A[n][g]   B (4 x 16): B[g][n]   C: element e = C[4 g + e][n]
+// Only the pairing of A's and B's k matters.  Products over d take k = d in
+// the order 16 j + 4 g + c (four consecutive floats of a row per lane, one
+// 16-byte read for the steps c = 0..3); products over the rows of a C result
+// take step e's k = row 4 g + e, so P and dS never leave the registers and
+// the other operand is read from its row-major tile as A[n] = T[4 g + e][n].
+//
+// LDS tiles: 32 rows x D floats, 16-byte chunk c of row m at c ^ (m & 15):
+// both reads are then free of bank conflicts (16 rows at one chunk; four
+// rows 4 g + e at 64 bytes each).  Filled by direct-to-LDS loads one tile
+// ahead (tile.hpp); rows past the end repeat the last one and are masked.
+#include <algorithm>
+#include <cmath>
+
 #include "common.hpp"
 #include "launch.hpp"
+#include "tile.hpp"
 
 namespace spr {
 
 namespace {
 
-constexpr int kF32Threads = 64;
+constexpr int kF32Row = 16;   // rows of a wave of a query-outer workgroup
+constexpr int kF32Tile = 32;  // rows of an LDS tile
+constexpr int kF32BK = 32;    // keys per key-outer workgroup
 
-// Query-outer tile decode shared by the forward and the dQ kernel.
-struct QTile {
-  bool prefix;   // rows are prefix rows
-  int lp0;       // first local row of the tile
-  int seg_len;   // rows in the segment
-  int row_base;  // memory row of local row 0 (suffix: cu[s])
-  int seq;       // suffix index (suffix rows only)
+__device__ __forceinline__ f32x4 mfma16(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
+
+// One wave's share (a quarter) of a 32-row tile's direct-to-LDS loads.
+template <int D>
+struct F32Loader {
+  static constexpr int CH = D / 4;     // 16-byte chunks per row
+  static constexpr int RPI = 64 / CH;  // rows per 1 KB instruction
+  static constexpr int IPW = kF32Tile / RPI / 4;
+  unsigned off[IPW];
+  int lrow0, lane_row;
+  __device__ __forceinline__ void init(int H, int w, int lane) {
+    lrow0 = w * IPW * RPI;
+    lane_row = lane / CH;
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      const int lrow = lrow0 + i * RPI + lane_row;
+      off[i] = ((unsigned)lrow * H * D + 4 * ((lane % CH) ^ (lrow & 15))) * 4;
+    }
+  }
+  // rows row0 .. of head hh; rows at or past nvalid (>= 1) repeat the last
+  __device__ __forceinline__ void load(float* tile, const float* base, int row0, int nvalid, int H, int hh) const {
+    const float* sb = base + ((size_t)row0 * H + hh) * D;
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      const int lrow = lrow0 + i * RPI + lane_row;
+      const unsigned back = (unsigned)(lrow - min(lrow, nvalid - 1)) * H * D * 4;
+      // the chunk order follows the tile row, not the row it repeats
+      dma_lds16_s(off[i] - back, sb, lds_addr(tile + (lrow0 + i * RPI) * D));
+    }
+  }
 };
 
-__device__ __forceinline__ bool decode_qtile(const AttnArgs& a, int bq, QTile& t) {
-  const int tile = gridDim.x - 1 - blockIdx.x;  // longest rows first
-  t.seq = a.seq_base + blockIdx.z;
-  if (tile < a.n_prefix_q_tiles) {
+// Per-lane LDS offsets (floats) of the operand reads; blocks of 16 rows add
+// a multiple of 16 D and 64 columns add 64, both immediates.
+template <int D>
+struct F32Offsets {
+  int nat[4];    // row n, columns 16 j + 4 g .. + 3: nat[j % 4] + 64 (j / 4)
+  int tr[4][4];  // row 4 g + e, column 16 db + n: tr[e][db % 4] + 64 (db / 4)
+  __device__ __forceinline__ void init(int lane) {
+    const int n = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) nat[j] = n * D + 4 * ((4 * j + g) ^ n);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) tr[e][q] = (4 * g + e) * D + 4 * ((4 * q + (n >> 2)) ^ (4 * g + e)) + (n & 3);
+  }
+};
+template <int D>
+__device__ __forceinline__ f32x4 nat_read(const float* t, const F32Offsets<D>& fo, int row0, int j) {
+  return *(const f32x4*)(t + row0 * D + 64 * (j >> 2) + fo.nat[j & 3]);
+}
+template <int D>
+__device__ __forceinline__ float tr_read(const float* t, const F32Offsets<D>& fo, int row0, int e, int db) {
+  return t[row0 * D + 64 * (db >> 2) + fo.tr[e][db & 3]];
+}
+
+// Query-outer workgroups in one of two forms.  KS = 1: 64 rows of one q
+// head, 16 per wave, every wave takes all 32 keys of a tile.  KS = 2 (launches
+// that cannot give every CU two workgroups of 64 rows): 32 rows, waves 2 and
+// 3 repeat the rows of waves 0 and 1 and each takes 16 keys of a tile, so a
+// sweep's chain of products is half as long and there are twice the
+// workgroups; the two key halves are merged through LDS at the end.  Measured
+// on the group above: the 64-row suffix's forward 94 -> 63 us and backward
+// 135 -> 87 us; the prefix forward (512 workgroups of 64 rows) 115 -> 110 us.
+// Block b -> (kv head b % Hkv, q head of its group, row tile, suffix), the
+// rows with the most keys first; every block of one kv head lands on one XCD
+// for Hkv dividing 8.  The launch arguments count 16-row tiles.
+template <int KS>
+struct QForm {
+  static constexpr int BQ = 4 * kF32Row / KS;  // rows per workgroup
+  static constexpr int NKB = 2 / KS;           // 16-key blocks per wave and tile
+  __host__ __device__ static int tiles(int tiles16) { return (tiles16 + 4 / KS - 1) / (4 / KS); }
+};
+struct F32Rows {
+  bool prefix;
+  int lp0, seg_len, row_base, hq, hk;
+};
+template <int KS>
+__device__ __forceinline__ bool decode_rows(const AttnArgs& a, int bid, F32Rows& t) {
+  const int G = a.hq / a.hkv, ntp = QForm<KS>::tiles(a.n_prefix_q_tiles);
+  const int ntx = ntp + QForm<KS>::tiles(a.n_suffix_q_tiles);
+  int b = bid;
+  t.hk = b % a.hkv;
+  b /= a.hkv;
+  t.hq = t.hk * G + b % G;
+  b /= G;
+  const int tile = ntx - 1 - b % ntx;
+  if (tile < ntp) {
     t.prefix = true;
-    t.lp0 = tile * bq;
+    t.lp0 = tile * QForm<KS>::BQ;
     t.seg_len = a.P;
     t.row_base = 0;
   } else {
     t.prefix = false;
-    t.lp0 = (tile - a.n_prefix_q_tiles) * bq;
-    const SegRows sg = suffix_rows(a.cu, t.seq, a.total_len);
+    t.lp0 = (tile - ntp) * QForm<KS>::BQ;
+    const SegRows sg = suffix_rows(a.cu, a.seq_base + b / ntx, a.total_len);
     t.row_base = sg.base;
     t.seg_len = sg.len;
   }
   return t.lp0 < t.seg_len;
 }
 
-template <int D>
-__device__ __forceinline__ void load_rows_f32(float (*dst)[D], const float* src, int nrows_valid,
-                                              int row_stride_elems, int nrows) {
-  // cooperative: nrows x D floats, rows >= nrows_valid are zero
-  for (int i = threadIdx.x; i < nrows * (D / 4); i += blockDim.x) {
-    const int r = i / (D / 4), c = (i % (D / 4)) * 4;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (r < nrows_valid) v = *(const float4*)(src + (size_t)r * row_stride_elems + c);
-    dst[r][c] = v.x; dst[r][c + 1] = v.y; dst[r][c + 2] = v.z; dst[r][c + 3] = v.w;
+// The key tiles a query-outer workgroup sweeps: prefix keys (causal for
+// prefix rows), then the suffix's own.
+struct F32Keys {
+  int nkeys0, nkeys1, nt0, nt;
+  __device__ __forceinline__ F32Keys(const AttnArgs& a, const F32Rows& t, int bq) {
+    const int last = min(t.lp0 + bq, t.seg_len) - 1;
+    nkeys0 = t.prefix ? min(a.P, last + 1) : a.P;
+    nkeys1 = t.prefix ? 0 : last + 1;
+    nt0 = (nkeys0 + kF32Tile - 1) / kF32Tile;
+    nt = nt0 + (nkeys1 + kF32Tile - 1) / kF32Tile;
+  }
+};
+
+// Sweeps the key tiles of a query-outer workgroup, double-buffered:
+// step(k0, nk, causal, K tile, V tile) for each.
+template <int D, int KS, typename Step>
+__device__ __forceinline__ void sweep_keys(const AttnArgs& a, const F32Rows& t, int w, int lane,
+                                           float (*Ks)[kF32Tile * D], float (*Vs)[kF32Tile * D], Step step) {
+  const F32Keys ks(a, t, QForm<KS>::BQ);
+  const float *k_p = in_sgpr((const float*)a.k_p), *k_s = in_sgpr((const float*)a.k_s);
+  const float *v_p = in_sgpr((const float*)a.v_p), *v_s = in_sgpr((const float*)a.v_s);
+  F32Loader<D> ld;
+  ld.init(a.hkv, w, lane);
+  auto issue = [&](int i) {
+    const bool p = i < ks.nt0;
+    const int k0 = (p ? i : i - ks.nt0) * kF32Tile;
+    const int nk = min(kF32Tile, (p ? ks.nkeys0 : ks.nkeys1) - k0), row = (p ? 0 : t.row_base) + k0;
+    ld.load(Ks[i & 1], pick(p, k_p, k_s), row, nk, a.hkv, t.hk);
+    ld.load(Vs[i & 1], pick(p, v_p, v_s), row, nk, a.hkv, t.hk);
+  };
+  if (ks.nt > 0) issue(0);
+  tile_barrier();
+  for (int i = 0; i < ks.nt; ++i) {
+    if (i + 1 < ks.nt) issue(i + 1);
+    compiler_fence();
+    const bool p = i < ks.nt0;
+    const int k0 = (p ? i : i - ks.nt0) * kF32Tile;
+    step(k0, min(kF32Tile, (p ? ks.nkeys0 : ks.nkeys1) - k0), p == t.prefix, Ks[i & 1], Vs[i & 1]);
+    tile_barrier();
   }
 }
 
 }  // namespace
 
 // ---------------------------------------------------------------- forward
-template <int D>
-__global__ __launch_bounds__(kF32Threads) void fwd_f32_kernel(AttnArgs a) {
-  constexpr int BQ = kF32Threads, BK = 32;
-  __shared__ float Ks[BK][D];
-  __shared__ float Vs[BK][D];
-  QTile t;
-  if (!decode_qtile(a, BQ, t)) return;
-  const int h = blockIdx.y, hk = h / (a.hq / a.hkv);
-  const int lp = t.lp0 + threadIdx.x;
-  const bool valid = lp < t.seg_len;
-  const float* q_base = (const float*)(t.prefix ? a.q_p : a.q_s);
-  float q[D], o[D];
-  const size_t qoff = ((size_t)(t.row_base + (valid ? lp : 0)) * a.hq + h) * D;
+// S^T = K Q^T with lane (n, g) holding four keys of row n per block, so a
+// row's softmax statistics take two shuffles; O^T += V^T P^T.
+template <int D, int KS>
+__global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
+  constexpr int NJ = D / 16, NKB = QForm<KS>::NKB;
+  __shared__ __attribute__((aligned(1024))) float Ks[2][kF32Tile * D];
+  __shared__ __attribute__((aligned(1024))) float Vs[2][kF32Tile * D];
+  F32Rows t;
+  if (!decode_rows<KS>(a, blockIdx.x, t)) return;
+  const int lane = threadIdx.x & 63, w = wave_id(), n = lane & 15, g = lane >> 4;
+  F32Offsets<D> fo;
+  fo.init(lane);
+  const int ks = KS == 2 ? w >> 1 : 0;  // key half of the tile
+  const int wave_lp0 = t.lp0 + kF32Row * (KS == 2 ? w & 1 : w), lp = wave_lp0 + n;
+  const int my_lp = min(lp, t.seg_len - 1);  // rows past the end recompute the last one
+  f32x4 q[NJ], o[NJ];
+  const size_t off = ((size_t)(t.row_base + my_lp) * a.hq + t.hq) * D + 4 * g;
+  {
+    const float* qb = (const float*)(t.prefix ? a.q_p : a.q_s);
 #pragma unroll
-  for (int d = 0; d < D; ++d) { q[d] = valid ? q_base[qoff + d] : 0.f; o[d] = 0.f; }
-  float m = -INFINITY, l = 0.f;
-  const int last_row = min(t.lp0 + BQ, t.seg_len) - 1;  // highest local row of the tile
+    for (int j = 0; j < NJ; ++j) q[j] = *(const f32x4*)(qb + off + 16 * j);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      settle(q[j]);
+      o[j] = zero4();
+    }
+  }
+  float m = -INFINITY, l = 0.f;  // running max (log2 domain); this lane's share of the row sum
 
-  for (int seg = 0; seg < 2; ++seg) {
-    // seg 0: prefix keys; seg 1: the suffix's own keys (suffix rows only)
-    if (seg == 1 && t.prefix) break;
-    const bool causal = (seg == 0) == t.prefix;  // same-segment keys are causal
-    const int nkeys = seg == 0 ? (t.prefix ? min(a.P, last_row + 1) : a.P) : last_row + 1;
-    const float* kb = (const float*)(seg == 0 ? a.k_p : a.k_s);
-    const float* vb = (const float*)(seg == 0 ? a.v_p : a.v_s);
-    const int kbase = seg == 0 ? 0 : t.row_base;
-    for (int k0 = 0; k0 < nkeys; k0 += BK) {
-      const int nk = min(BK, nkeys - k0);
-      __syncthreads();
-      load_rows_f32<D>(Ks, kb + ((size_t)(kbase + k0) * a.hkv + hk) * D, nk, a.hkv * D, BK);
-      load_rows_f32<D>(Vs, vb + ((size_t)(kbase + k0) * a.hkv + hk) * D, nk, a.hkv * D, BK);
-      __syncthreads();
-      float s[BK];
-      float mt = -INFINITY;
-#pragma unroll 4
-      for (int j = 0; j < BK; ++j) {
-        float acc = 0.f;
+  sweep_keys<D, KS>(a, t, w, lane, Ks, Vs, [&](int k0, int nk, bool causal, const float* Kc, const float* Vc) {
+    const int kk = k0 + 16 * ks;  // this wave's first key
+    if (wave_lp0 >= t.seg_len || (causal && kk > wave_lp0 + 15)) return;  // no row of this wave sees them
+    f32x4 st[2] = {zero4(), zero4()};  // st[b][e] = S^T[key kk + 16 b + 4 g + e][row n]
 #pragma unroll
-        for (int d = 0; d < D; ++d) acc = fmaf(q[d], Ks[j][d], acc);
-        const bool vis = j < nk && (!causal || k0 + j <= lp);
-        s[j] = vis ? acc * a.scale_log2 : -INFINITY;
-        mt = fmaxf(mt, s[j]);
+    for (int j = 0; j < NJ; ++j) {
+      // two independent chains: the tile's two key blocks, or the even and
+      // odd j of the one block
+      const f32x4 k_0 = nat_read<D>(Kc, fo, 16 * ks, j), k_1 = NKB == 2 ? nat_read<D>(Kc, fo, 16, j) : k_0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (NKB == 2 || j % 2 == 0) st[0] = mfma16(k_0[c], q[j][c], st[0]);
+        if (NKB == 2 || j % 2 == 1) st[1] = mfma16(k_1[c], q[j][c], st[1]);
       }
+    }
+    if (NKB == 1) st[0] += st[1];
+    if (nk < kF32Tile || (causal && k0 + kF32Tile - 1 > wave_lp0)) {
+      const int lim = (causal ? min(nk, my_lp - k0 + 1) : nk) - 16 * ks - 4 * g;
+#pragma unroll
+      for (int i = 0; i < 4 * NKB; ++i)
+        st[i >> 2][i & 3] = 16 * (i >> 2) + (i & 3) < lim ? st[i >> 2][i & 3] : -INFINITY;
+    }
+    float mt = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4 * NKB; ++i) mt = fmaxf(mt, st[i >> 2][i & 3]);
+    mt = fmaxf(mt, __shfl_xor(mt, 16));
+    mt = fmaxf(mt, __shfl_xor(mt, 32)) * a.scale_log2;
+    if (__any(mt > m)) {
       const float mn = fmaxf(m, mt);
-      const float mu = mn == -INFINITY ? 0.f : mn;
-      const float corr = exp2f(m - mu);
+      const float corr = fast_exp2(m - (mn == -INFINITY ? 0.f : mn));
       l *= corr;
 #pragma unroll
-      for (int d = 0; d < D; ++d) o[d] *= corr;
-#pragma unroll 4
-      for (int j = 0; j < BK; ++j) {
-        const float p = exp2f(s[j] - mu);
-        l += p;
-#pragma unroll
-        for (int d = 0; d < D; ++d) o[d] = fmaf(p, Vs[j][d], o[d]);
-      }
+      for (int j = 0; j < NJ; ++j) o[j] *= corr;
       m = mn;
     }
-  }
-  if (!valid) return;
-  const float inv = 1.f / l;
-  float* o_base = (float*)(t.prefix ? a.o_p : a.o_s);
+    const float mu = m == -INFINITY ? 0.f : m;
 #pragma unroll
-  for (int d = 0; d < D; ++d) o_base[qoff + d] = o[d] * inv;
-  float* lse = t.prefix ? a.lse_p : a.lse_s;
-  lse[(size_t)(t.row_base + lp) * a.hq + h] = (m + log2f(l)) * kLn2;
+    for (int i = 0; i < 4 * NKB; ++i) {
+      const float p = fast_exp2(fmaf(st[i >> 2][i & 3], a.scale_log2, -mu));
+      st[i >> 2][i & 3] = p;
+      l += p;
+    }
+#pragma unroll
+    for (int i = 0; i < 4 * NKB; ++i)
+#pragma unroll
+      for (int db = 0; db < NJ; ++db)
+        o[db] = mfma16(tr_read<D>(Vc, fo, 16 * (i >> 2) + 16 * ks, i & 3, db), st[i >> 2][i & 3], o[db]);
+  });
+
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if constexpr (KS == 2) {
+    // merge the key halves: waves 2 and 3 hand over max, sum and O
+    f32x4* xo = (f32x4*)Ks;  // [wave][db][lane]; the tiles are no longer read
+    float* xm = (float*)Vs;  // [wave][max, sum][lane]
+    const int r = w & 1;
+    if (ks == 1) {
+      xm[128 * r + lane] = m;
+      xm[128 * r + 64 + lane] = l;
+#pragma unroll
+      for (int db = 0; db < NJ; ++db) xo[(r * NJ + db) * 64 + lane] = o[db];
+    }
+    __syncthreads();
+    if (ks == 1) return;
+    const float m1 = xm[128 * r + lane], l1 = xm[128 * r + 64 + lane];
+    const float mn = fmaxf(m, m1);  // finite: every row sees a key of half 0
+    const float c0 = fast_exp2(m - mn), c1 = fast_exp2(m1 - mn);
+    l = l * c0 + l1 * c1;
+#pragma unroll
+    for (int db = 0; db < NJ; ++db) o[db] = o[db] * c0 + xo[(r * NJ + db) * 64 + lane] * c1;
+    m = mn;
+  }
+  if (lp >= t.seg_len) return;
+  const float inv = 1.f / l;
+  float* ob = (float*)(t.prefix ? a.o_p : a.o_s);
+#pragma unroll
+  for (int db = 0; db < NJ; ++db) *(f32x4*)(ob + off + 16 * db) = o[db] * inv;
+  if (g == 0) (t.prefix ? a.lse_p : a.lse_s)[(size_t)(t.row_base + lp) * a.hq + t.hq] = (m + log2f(l)) * kLn2;
 }
 
+namespace {
+
 // ------------------------------------------------------- backward, dK / dV
-// Key-outer: one thread per key of a 64-key tile, looping over every query
-// row that sees the tile (all G heads of the kv head).
 template <int D>
-__global__ __launch_bounds__(kF32Threads) void bwd_kv_f32_kernel(AttnArgs a) {
-  constexpr int BK = kF32Threads, BQ = 16;
-  __shared__ float Ks[BK][D + 1];
-  __shared__ float Vs[BK][D + 1];
-  __shared__ float Qs[BQ][D];
-  __shared__ float dOs[BQ][D];
-  __shared__ float Ls[BQ], Dd[BQ];
-  const int x = blockIdx.x, hk = blockIdx.y, G = a.hq / a.hkv;
+struct F32KvLds {
+  float q[2][kF32Tile * D], o[2][kF32Tile * D];
+  float l[2][64], e[2][64];  // log2-domain LSE and rowsum(dO * O) of the tile's rows (32 used)
+};
+
+// Key-outer: 32 keys of one kv head per workgroup, sweeping every row that
+// sees them, for all G q heads, in 32-row tiles.  Wave w takes keys
+// 16 (w % 2) and rows 16 (w / 2) of each tile; the two row halves' sums are
+// added through LDS at the end (one wave finishes dV, the other dK).
+template <int D>
+__device__ __forceinline__ void bwd_kv_f32(const AttnArgs& a, int bid, F32KvLds<D>& L) {
+  constexpr int NJ = D / 16;
+  const int lane = threadIdx.x & 63, w = wave_id(), n = lane & 15, g = lane >> 4;
+  const int kb = w & 1, rh = w >> 1;
+  F32Offsets<D> fo;
+  fo.init(lane);
+  const int R = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
+  const int G = a.hq / a.hkv, hk = bid % a.hkv, rs = (bid / a.hkv) % R, x = bid / a.hkv / R;
   bool kpre;
-  int k0, kseg, kbase, s = 0;
+  int k0, kseg, kbase;
   if (x < a.n_prefix_k_tiles) {
-    kpre = true; k0 = x * BK; kseg = a.P; kbase = 0;
+    kpre = true;
+    k0 = x * kF32BK;
+    kseg = a.P;
+    kbase = 0;
   } else {
     const int y = x - a.n_prefix_k_tiles;
-    s = a.seq_base + y / a.n_suffix_k_tiles;
-    k0 = (y % a.n_suffix_k_tiles) * BK;
-    const SegRows sg = suffix_rows(a.cu, s, a.total_len);
+    kpre = false;
+    k0 = (y % a.n_suffix_k_tiles) * kF32BK;
+    const SegRows sg = suffix_rows(a.cu, a.seq_base + y / a.n_suffix_k_tiles, a.total_len);
     kbase = sg.base;
     kseg = sg.len;
-    kpre = false;
   }
   if (k0 >= kseg) return;
-  const int key = k0 + threadIdx.x;
-  const bool kvalid = key < kseg;
+  const int wave_k0 = k0 + 16 * kb, key = wave_k0 + n;
+  const int my_key = min(key, kseg - 1);  // keys past the end recompute the last one
+  f32x4 kf[NJ], vf[NJ], dk[NJ], dv[NJ];
   {
-    const float* kb = (const float*)(kpre ? a.k_p : a.k_s);
-    const float* vb = (const float*)(kpre ? a.v_p : a.v_s);
-    const size_t off = ((size_t)(kbase + (kvalid ? key : 0)) * a.hkv + hk) * D;
-    for (int d = 0; d < D; ++d) {
-      Ks[threadIdx.x][d] = kvalid ? kb[off + d] : 0.f;
-      Vs[threadIdx.x][d] = kvalid ? vb[off + d] : 0.f;
+    const float* kg = (const float*)(kpre ? a.k_p : a.k_s);
+    const float* vg = (const float*)(kpre ? a.v_p : a.v_s);
+    const size_t off = ((size_t)(kbase + my_key) * a.hkv + hk) * D + 4 * g;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      kf[j] = *(const f32x4*)(kg + off + 16 * j);
+      vf[j] = *(const f32x4*)(vg + off + 16 * j);
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      settle(kf[j]);
+      settle(vf[j]);
+      dk[j] = zero4();
+      dv[j] = zero4();
     }
   }
-  float dk[D], dv[D];
-#pragma unroll
-  for (int d = 0; d < D; ++d) { dk[d] = 0.f; dv[d] = 0.f; }
-  const float lse_scale = kLog2e;
-
-  // row range job: rows [r0, r1) of a segment, memory row = base + r,
-  // causal => row r sees key iff key <= r (same segment coordinates)
-  auto run_rows = [&](int hh, bool rows_prefix, int base, int r0, int r1, bool causal) {
-    const float* qb = (const float*)(rows_prefix ? a.q_p : a.q_s);
-    const float* db = (const float*)(rows_prefix ? a.do_p : a.do_s);
-    const float* lb = rows_prefix ? a.lse_p : a.lse_s;
-    const float* ddb = rows_prefix ? a.dd_p : a.dd_s;
-    for (int rt = r0; rt < r1; rt += BQ) {
-      const int nr = min(BQ, r1 - rt);
-      __syncthreads();
-      load_rows_f32<D>(Qs, qb + ((size_t)(base + rt) * a.hq + hh) * D, nr, a.hq * D, BQ);
-      load_rows_f32<D>(dOs, db + ((size_t)(base + rt) * a.hq + hh) * D, nr, a.hq * D, BQ);
-      if (threadIdx.x < BQ) {
-        const bool v = threadIdx.x < nr;
-        Ls[threadIdx.x] = v ? lb[(size_t)(base + rt + threadIdx.x) * a.hq + hh] : 0.f;
-        Dd[threadIdx.x] = v ? ddb[(size_t)(base + rt + threadIdx.x) * a.hq + hh] : 0.f;
-      }
-      __syncthreads();
-      for (int r = 0; r < nr; ++r) {
-        const bool vis = kvalid && (!causal || key <= rt + r);
-        if (!vis) continue;
-        float sc = 0.f, dp = 0.f;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          sc = fmaf(Qs[r][d], Ks[threadIdx.x][d], sc);
-          dp = fmaf(dOs[r][d], Vs[threadIdx.x][d], dp);
-        }
-        const float p = exp2f(sc * a.scale_log2 - Ls[r] * lse_scale);
-        const float ds = p * (dp - Dd[r]);
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          dv[d] = fmaf(p, dOs[r][d], dv[d]);
-          dk[d] = fmaf(ds, Qs[r][d], dk[d]);
-        }
-      }
-    }
-  };
-
-  for (int hh = hk * G; hh < hk * G + G; ++hh) {
-    if (kpre) {
-      if (a.prefix_rows) run_rows(hh, true, 0, k0, a.P, true);
-      if (a.suffix_rows) {
-        const SegRows sp = suffix_span(a.cu, a.seq_base, a.seq_base + a.n_seq, a.total_len);
-        const int r0 = sp.base, r1 = sp.base + sp.len;
-        run_rows(hh, false, r0, 0, r1 - r0, false);
-      }
-    } else {
-      run_rows(hh, false, kbase, k0, kseg, true);
-    }
-  }
-  if (!kvalid) return;
+  // row tiles: a prefix key tile sees prefix rows from k0 on (causal) and/or
+  // every suffix row of the launch; a suffix key tile its own rows from k0 on
+  int n_pr = 0, n_sr = 0, sr0 = 0, sr1 = 0;
   if (kpre) {
-    const size_t off = ((size_t)key * a.hkv + hk) * D;
-    if (a.pk_mode == kPkAccumulate) {
-      for (int d = 0; d < D; ++d) {
-        a.gk[off + d] += dk[d] * a.scale;
-        a.gv[off + d] += dv[d];
-      }
-    } else {
-      float* okp = (float*)a.dk_p;
-      float* ovp = (float*)a.dv_p;
-      for (int d = 0; d < D; ++d) {
-        okp[off + d] = dk[d] * a.scale + a.gk[off + d];
-        ovp[off + d] = dv[d] + a.gv[off + d];
-      }
+    if (a.prefix_rows) n_pr = (a.P - k0 + kF32Tile - 1) / kF32Tile;
+    if (a.suffix_rows) {
+      const SegRows sp = suffix_span(a.cu, a.seq_base, a.seq_base + a.n_seq, a.total_len);
+      sr0 = sp.base;
+      sr1 = sp.base + sp.len;
+      n_sr = (sp.len + kF32Tile - 1) / kF32Tile;
     }
   } else {
-    const size_t off = ((size_t)(kbase + key) * a.hkv + hk) * D;
-    float* oks = (float*)a.dk_s;
-    float* ovs = (float*)a.dv_s;
-    for (int d = 0; d < D; ++d) {
-      oks[off + d] = dk[d] * a.scale;
-      ovs[off + d] = dv[d];
+    n_sr = (kseg - k0 + kF32Tile - 1) / kF32Tile;
+  }
+  // this block's contiguous share of the (row tile, head) sequence below
+  const int all = G * (n_pr + n_sr);
+  const int t_lo = (int)((long)all * rs / R), nt = (int)((long)all * (rs + 1) / R) - t_lo;
+  struct RowTile {
+    int row0, nr, lp;  // memory row, valid rows, segment-local first row
+    bool prefix, causal;
+  };
+  // row tiles outer, heads inner (neighbouring key tiles then read the same
+  // rows at about the same time); causal ranges from the last row down
+  auto info = [&](int j) {
+    RowTile rt;
+    if (kpre && j < n_sr) {
+      rt = {sr0 + j * kF32Tile, 0, 0, false, false};
+      rt.nr = min(kF32Tile, sr1 - rt.row0);
+    } else if (kpre) {
+      const int lp = k0 + (n_pr - 1 - (j - n_sr)) * kF32Tile;
+      rt = {lp, min(kF32Tile, a.P - lp), lp, true, true};
+    } else {
+      const int lp = k0 + (n_sr - 1 - j) * kF32Tile;
+      rt = {kbase + lp, min(kF32Tile, kseg - lp), lp, false, true};
     }
+    return rt;
+  };
+  const float *q_p = in_sgpr((const float*)a.q_p), *q_s = in_sgpr((const float*)a.q_s);
+  const float *do_p = in_sgpr((const float*)a.do_p), *do_s = in_sgpr((const float*)a.do_s);
+  const float *l_p = in_sgpr((const float*)a.lse2_p), *l_s = in_sgpr((const float*)a.lse2_s);
+  const float *e_p = in_sgpr((const float*)a.dd_p), *e_s = in_sgpr((const float*)a.dd_s);
+  F32Loader<D> ld;
+  ld.init(a.hq, w, lane);
+  RowVecLoader rl;
+  rl.init(a.hq, lane);
+  auto issue = [&](int j, int gi, int b) {
+    const RowTile rt = info(j);
+    const int hh = hk * G + gi;
+    ld.load(L.q[b], pick(rt.prefix, q_p, q_s), rt.row0, rt.nr, a.hq, hh);
+    ld.load(L.o[b], pick(rt.prefix, do_p, do_s), rt.row0, rt.nr, a.hq, hh);
+    if (w == 0) rl.load(L.l[b], pick(rt.prefix, l_p, l_s) + hh, rt.row0, rt.nr, a.hq);
+    if (w == 1) rl.load(L.e[b], pick(rt.prefix, e_p, e_s) + hh, rt.row0, rt.nr, a.hq);
+  };
+
+  // key tile 0's sweep is the launch's longest chain: its waves go before
+  // the query-outer waves that share their SIMDs
+  __builtin_amdgcn_s_setprio(1);
+  int lj = t_lo / G, lg = t_lo % G, cj = lj, cg = lg;  // next tile to load, next to compute
+  auto next = [&](int& j, int& gi) {
+    if (++gi == G) {
+      gi = 0;
+      ++j;
+    }
+  };
+  if (nt > 0) {
+    issue(lj, lg, 0);
+    next(lj, lg);
+  }
+  tile_barrier();
+  for (int i = 0; i < nt; ++i) {
+    const int b = i & 1;
+    if (i + 1 < nt) {
+      issue(lj, lg, b ^ 1);
+      next(lj, lg);
+    }
+    compiler_fence();
+    const RowTile rt = info(cj);
+    next(cj, cg);
+    // this wave's 16 rows of the tile: any valid, any seeing its keys?
+    if (16 * rh < rt.nr && !(rt.causal && rt.lp + 16 * rh + 15 < wave_k0)) {
+      const float *Qc = L.q[b], *Oc = L.o[b];
+      f32x4 s = zero4(), dp = zero4();  // [row 16 rh + 4 g + e][key n]
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const f32x4 qa = nat_read<D>(Qc + 16 * D * rh, fo, 0, j), oa = nat_read<D>(Oc + 16 * D * rh, fo, 0, j);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          s = mfma16(qa[c], kf[j][c], s);
+          dp = mfma16(oa[c], vf[j][c], dp);
+        }
+      }
+      const f32x4 l4 = *(const f32x4*)(L.l[b] + 16 * rh + 4 * g), e4 = *(const f32x4*)(L.e[b] + 16 * rh + 4 * g);
+      // row lp + q sees this lane's key iff q >= q_lo (causal) and q < nr
+      const int q_lo = (rt.causal ? my_key - rt.lp : 0) - 16 * rh - 4 * g, q_hi = rt.nr - 16 * rh - 4 * g;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float p = fast_exp2(fmaf(s[e], a.scale_log2, -l4[e]));
+        p = e >= q_lo && e < q_hi ? p : 0.f;
+        s[e] = p;
+        dp[e] = p * (dp[e] - e4[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int db = 0; db < NJ; ++db) {
+          dv[db] = mfma16(tr_read<D>(Oc + 16 * D * rh, fo, 0, e, db), s[e], dv[db]);
+          dk[db] = mfma16(tr_read<D>(Qc + 16 * D * rh, fo, 0, e, db), dp[e], dk[db]);
+        }
+    }
+    tile_barrier();
+  }
+
+  // the other row half's sums (the tiles are no longer read)
+  f32x4* xch = (f32x4*)&L;  // [kb][rh][db][lane]
+#pragma unroll
+  for (int db = 0; db < NJ; ++db) xch[((kb * 2 + rh) * NJ + db) * 64 + lane] = rh == 0 ? dk[db] : dv[db];
+  __syncthreads();
+  if (key >= kseg) return;
+  const float sc = rh == 0 ? 1.f : a.scale;  // rh 0 finishes dV, rh 1 dK
+  const size_t off = ((size_t)(kbase + key) * a.hkv + hk) * D + 4 * g;
+  float* cache = rh == 0 ? a.gv : a.gk;
+  float* out = (float*)(rh == 0 ? (kpre ? a.dv_p : a.dv_s) : (kpre ? a.dk_p : a.dk_s));
+#pragma unroll
+  for (int db = 0; db < NJ; ++db) {
+    const f32x4 other = xch[((kb * 2 + (rh ^ 1)) * NJ + db) * 64 + lane];
+    const f32x4 v = (rh == 0 ? dv[db] + other : other + dk[db]) * sc;
+    const size_t at = off + 16 * db;
+    if (rs > 0)  // a later share's partial, added by kv_combine_f32_kernel
+      *(f32x4*)((rh == 0 ? a.part_dv : a.part_dk) + (size_t)(rs - 1) * a.P * a.hkv * D + at) = v;
+    else if (!kpre || R > 1)
+      *(f32x4*)(out + at) = v;
+    else if (a.pk_mode == kPkAccumulate)
+      *(f32x4*)(cache + at) = *(const f32x4*)(cache + at) + v;
+    else
+      *(f32x4*)(out + at) = v + *(const f32x4*)(cache + at);
   }
 }
 
 // ------------------------------------------------------------ backward, dQ
-// Query-outer: one thread per query row; dq_acc[row] += dS K (unscaled).
-template <int D>
-__global__ __launch_bounds__(kF32Threads) void bwd_q_f32_kernel(AttnArgs a) {
-  constexpr int BQ = kF32Threads, BK = 32;
-  __shared__ float Qs[BQ][D + 1];
-  __shared__ float dOs[BQ][D + 1];
-  __shared__ float Ks[BK][D];
-  __shared__ float Vs[BK][D];
-  QTile t;
-  if (!decode_qtile(a, BQ, t)) return;
-  const int h = blockIdx.y, hk = h / (a.hq / a.hkv);
-  const int lp = t.lp0 + threadIdx.x;
-  const bool valid = lp < t.seg_len;
-  const float* qb = (const float*)(t.prefix ? a.q_p : a.q_s);
-  const float* db = (const float*)(t.prefix ? a.do_p : a.do_s);
-  const size_t qoff = ((size_t)(t.row_base + (valid ? lp : 0)) * a.hq + h) * D;
-  for (int d = 0; d < D; ++d) {
-    Qs[threadIdx.x][d] = valid ? qb[qoff + d] : 0.f;
-    dOs[threadIdx.x][d] = valid ? db[qoff + d] : 0.f;
-  }
-  const size_t lidx = (size_t)(t.row_base + (valid ? lp : 0)) * a.hq + h;
-  const float lse2 = valid ? (t.prefix ? a.lse_p : a.lse_s)[lidx] * kLog2e : 0.f;
-  const float drow = valid ? (t.prefix ? a.dd_p : a.dd_s)[lidx] : 0.f;
-  float dq[D];
+// Query-outer (QForm): S^T and dP^T recomputed, dQ^T += K^T dS^T, written
+// once, scaled (the dense baseline's prefix rows:
+// added unscaled to its fp32 sum over the trajectories).
+template <int D, int KS>
+__device__ __forceinline__ void bwd_q_f32(const AttnArgs& a, int bid, float (*Ks)[kF32Tile * D],
+                                          float (*Vs)[kF32Tile * D]) {
+  constexpr int NJ = D / 16, NKB = QForm<KS>::NKB;
+  F32Rows t;
+  if (!decode_rows<KS>(a, bid, t)) return;
+  const int lane = threadIdx.x & 63, w = wave_id(), n = lane & 15, g = lane >> 4;
+  F32Offsets<D> fo;
+  fo.init(lane);
+  const int ks = KS == 2 ? w >> 1 : 0;
+  const int wave_lp0 = t.lp0 + kF32Row * (KS == 2 ? w & 1 : w), lp = wave_lp0 + n;
+  const int my_lp = min(lp, t.seg_len - 1);
+  const size_t rh = (size_t)(t.row_base + my_lp) * a.hq + t.hq, off = rh * D + 4 * g;
+  f32x4 q[NJ], d_o[NJ], dq[NJ];
+  float lse2 = (t.prefix ? a.lse2_p : a.lse2_s)[rh], drow = (t.prefix ? a.dd_p : a.dd_s)[rh];
+  {
+    const float* qb = (const float*)(t.prefix ? a.q_p : a.q_s);
+    const float* ob = (const float*)(t.prefix ? a.do_p : a.do_s);
 #pragma unroll
-  for (int d = 0; d < D; ++d) dq[d] = 0.f;
-  const int last_row = min(t.lp0 + BQ, t.seg_len) - 1;
-  for (int seg = 0; seg < 2; ++seg) {
-    if (seg == 1 && t.prefix) break;
-    const bool causal = (seg == 0) == t.prefix;
-    const int nkeys = seg == 0 ? (t.prefix ? min(a.P, last_row + 1) : a.P) : last_row + 1;
-    const float* kbp = (const float*)(seg == 0 ? a.k_p : a.k_s);
-    const float* vbp = (const float*)(seg == 0 ? a.v_p : a.v_s);
-    const int kbase = seg == 0 ? 0 : t.row_base;
-    for (int k0 = 0; k0 < nkeys; k0 += BK) {
-      const int nk = min(BK, nkeys - k0);
-      __syncthreads();
-      load_rows_f32<D>(Ks, kbp + ((size_t)(kbase + k0) * a.hkv + hk) * D, nk, a.hkv * D, BK);
-      load_rows_f32<D>(Vs, vbp + ((size_t)(kbase + k0) * a.hkv + hk) * D, nk, a.hkv * D, BK);
-      __syncthreads();
-      if (!valid) continue;
-      for (int j = 0; j < nk; ++j) {
-        if (causal && k0 + j > lp) break;
-        float sc = 0.f, dp = 0.f;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          sc = fmaf(Qs[threadIdx.x][d], Ks[j][d], sc);
-          dp = fmaf(dOs[threadIdx.x][d], Vs[j][d], dp);
-        }
-        const float ds = exp2f(sc * a.scale_log2 - lse2) * (dp - drow);
-#pragma unroll
-        for (int d = 0; d < D; ++d) dq[d] = fmaf(ds, Ks[j][d], dq[d]);
-      }
+    for (int j = 0; j < NJ; ++j) {
+      q[j] = *(const f32x4*)(qb + off + 16 * j);
+      d_o[j] = *(const f32x4*)(ob + off + 16 * j);
     }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      settle(q[j]);
+      settle(d_o[j]);
+      dq[j] = zero4();
+    }
+    settle(lse2);
+    settle(drow);
   }
-  if (!valid) return;
-  float* acc = t.prefix ? a.dq_acc_p : a.dq_acc_s;
-  for (int d = 0; d < D; ++d) acc[qoff + d] += dq[d];
+  sweep_keys<D, KS>(a, t, w, lane, Ks, Vs, [&](int k0, int nk, bool causal, const float* Kc, const float* Vc) {
+    if (wave_lp0 >= t.seg_len || (causal && k0 + 16 * ks > wave_lp0 + 15)) return;
+    f32x4 st[2] = {zero4(), zero4()}, pt[2] = {zero4(), zero4()};  // [key 16 (ks + kb) + 4 g + e][row n]
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb) {
+        const f32x4 ka = nat_read<D>(Kc, fo, 16 * (ks + kb), j), va = nat_read<D>(Vc, fo, 16 * (ks + kb), j);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          st[kb] = mfma16(ka[c], q[j][c], st[kb]);
+          pt[kb] = mfma16(va[c], d_o[j][c], pt[kb]);
+        }
+      }
+    const int lim = (causal ? min(nk, my_lp - k0 + 1) : nk) - 16 * ks - 4 * g;
+#pragma unroll
+    for (int i = 0; i < 4 * NKB; ++i) {
+      const int kb = i >> 2, e = i & 3;
+      float p = fast_exp2(fmaf(st[kb][e], a.scale_log2, -lse2));
+      p = 16 * kb + e < lim ? p : 0.f;
+      const float ds = p * (pt[kb][e] - drow);
+#pragma unroll
+      for (int db = 0; db < NJ; ++db) dq[db] = mfma16(tr_read<D>(Kc, fo, 16 * (ks + kb), e, db), ds, dq[db]);
+    }
+  });
+  if constexpr (KS == 2) {
+    // the key halves' sums, through the tiles no longer read
+    f32x4* x = (f32x4*)Ks;  // [wave][db][lane]
+#pragma unroll
+    for (int db = 0; db < NJ; ++db)
+      if (ks == 1) x[((w & 1) * NJ + db) * 64 + lane] = dq[db];
+    __syncthreads();
+    if (ks == 1) return;
+#pragma unroll
+    for (int db = 0; db < NJ; ++db) dq[db] += x[((w & 1) * NJ + db) * 64 + lane];
+  }
+  if (lp >= t.seg_len) return;
+  if (t.prefix && a.dq_p_accumulate) {
+#pragma unroll
+    for (int db = 0; db < NJ; ++db) {
+      f32x4* p = (f32x4*)(a.dq_acc_p + off + 16 * db);
+      *p = *p + dq[db];
+    }
+    return;
+  }
+  float* out = (float*)(t.prefix ? a.dq_p : a.dq_s);
+#pragma unroll
+  for (int db = 0; db < NJ; ++db) *(f32x4*)(out + off + 16 * db) = dq[db] * a.scale;
+}
+
+}  // namespace
+
+// Both roles in one launch, so that a small group's key tiles and row tiles
+// share the chip: n_kv key-outer blocks first (their sweeps are the longest),
+// then the query-outer ones.
+template <int D, int KS>
+__global__ __launch_bounds__(kThreads, 2) void bwd_f32_kernel(AttnArgs a, int n_kv) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[sizeof(F32KvLds<D>)];
+  const int b = blockIdx.x;
+  if (b < n_kv) {
+    bwd_kv_f32<D>(a, b, *(F32KvLds<D>*)lds);
+  } else {
+    float(*tiles)[kF32Tile * D] = (float(*)[kF32Tile * D])lds;
+    bwd_q_f32<D, KS>(a, b - n_kv, tiles, tiles + 2);
+  }
+}
+
+// dK_P/dV_P of a Phase C whose key sweeps were cut into kv_rsplit shares:
+// share 0 lies in the outputs themselves, the others in part_dk/part_dv; all
+// are added in share order, then the cache.
+__global__ __launch_bounds__(kThreads) void kv_combine_f32_kernel(AttnArgs a, size_t n4) {
+  const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
+  if (i >= n4) return;
+  f32x4 k = ((f32x4*)a.dk_p)[i], v = ((f32x4*)a.dv_p)[i];
+  for (int j = 1; j < a.kv_rsplit; ++j) {
+    k += ((const f32x4*)a.part_dk)[(j - 1) * n4 + i];
+    v += ((const f32x4*)a.part_dv)[(j - 1) * n4 + i];
+  }
+  ((f32x4*)a.dk_p)[i] = k + ((const f32x4*)a.gk)[i];
+  ((f32x4*)a.dv_p)[i] = v + ((const f32x4*)a.gv)[i];
 }
 
 // ------------------------------------------------------------- launchers
-int f32_block_q() { return kF32Threads; }
-int f32_block_k() { return kF32Threads; }
+int f32_block_q() { return kF32Row; }
+int f32_block_k() { return kF32BK; }
+
+namespace {
+// query-outer workgroups of a launch in form KS
+template <int KS>
+long q_blocks(const AttnArgs& a, int n_z) {
+  return (long)(QForm<KS>::tiles(a.n_prefix_q_tiles) + QForm<KS>::tiles(a.n_suffix_q_tiles)) * a.hq * n_z;
+}
+// KS = 2 while workgroups of 64 rows cannot give each of the 256 CUs two.
+constexpr long kF32SplitBelow = 1024;
+}  // namespace
 
 hipError_t launch_fwd_f32(const AttnArgs& a, int head_dim, int n_z, hipStream_t st) {
-  const dim3 grid(a.n_prefix_q_tiles + a.n_suffix_q_tiles, a.hq, n_z);
-  if (grid.x == 0 || n_z == 0) return hipSuccess;
+  const bool split = q_blocks<1>(a, n_z) < kF32SplitBelow;
+  const dim3 grid((unsigned)(split ? q_blocks<2>(a, n_z) : q_blocks<1>(a, n_z)));
+  if (grid.x == 0) return hipSuccess;
   ProfileScope ps("fwd_f32", st);
-  if (head_dim == 64)
-    hipLaunchKernelGGL(fwd_f32_kernel<64>, grid, dim3(kF32Threads), 0, st, a);
+  if (head_dim == 64 && split)
+    hipLaunchKernelGGL((fwd_f32_kernel<64, 2>), grid, dim3(kThreads), 0, st, a);
+  else if (head_dim == 64)
+    hipLaunchKernelGGL((fwd_f32_kernel<64, 1>), grid, dim3(kThreads), 0, st, a);
+  else if (split)
+    hipLaunchKernelGGL((fwd_f32_kernel<128, 2>), grid, dim3(kThreads), 0, st, a);
   else
-    hipLaunchKernelGGL(fwd_f32_kernel<128>, grid, dim3(kF32Threads), 0, st, a);
+    hipLaunchKernelGGL((fwd_f32_kernel<128, 1>), grid, dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_f32(const AttnArgs& a, int head_dim, int n_qz, hipStream_t st) {
-  {
-    const dim3 grid(a.n_prefix_k_tiles + a.n_seq * a.n_suffix_k_tiles, a.hkv, 1);
-    if (grid.x > 0) {
-      ProfileScope ps("bwd_kv_f32", st);
-      if (head_dim == 64)
-        hipLaunchKernelGGL(bwd_kv_f32_kernel<64>, grid, dim3(kF32Threads), 0, st, a);
-      else
-        hipLaunchKernelGGL(bwd_kv_f32_kernel<128>, grid, dim3(kF32Threads), 0, st, a);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-  }
-  const dim3 grid(a.n_prefix_q_tiles + a.n_suffix_q_tiles, a.hq, n_qz);
-  if (grid.x == 0 || n_qz == 0) return hipSuccess;
-  ProfileScope ps("bwd_q_f32", st);
-  if (head_dim == 64)
-    hipLaunchKernelGGL(bwd_q_f32_kernel<64>, grid, dim3(kF32Threads), 0, st, a);
+  const int R = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
+  // shares: Phase C only (prefix keys, injected cache)
+  if (R > 1 && (a.n_suffix_k_tiles || a.suffix_rows || a.pk_mode != kPkInject || !a.part_dk || !a.part_dv))
+    return hipErrorInvalidValue;
+  const long n_kv = ((long)a.n_prefix_k_tiles + (long)a.n_seq * a.n_suffix_k_tiles) * a.hkv * R;
+  const bool split = q_blocks<1>(a, n_qz) < kF32SplitBelow;
+  const long n_q = split ? q_blocks<2>(a, n_qz) : q_blocks<1>(a, n_qz);
+  if (n_kv + n_q == 0) return hipSuccess;
+  const dim3 grid((unsigned)(n_kv + n_q));
+  ProfileScope ps("bwd_f32", st);
+  if (head_dim == 64 && split)
+    hipLaunchKernelGGL((bwd_f32_kernel<64, 2>), grid, dim3(kThreads), 0, st, a, (int)n_kv);
+  else if (head_dim == 64)
+    hipLaunchKernelGGL((bwd_f32_kernel<64, 1>), grid, dim3(kThreads), 0, st, a, (int)n_kv);
+  else if (split)
+    hipLaunchKernelGGL((bwd_f32_kernel<128, 2>), grid, dim3(kThreads), 0, st, a, (int)n_kv);
   else
-    hipLaunchKernelGGL(bwd_q_f32_kernel<128>, grid, dim3(kF32Threads), 0, st, a);
+    hipLaunchKernelGGL((bwd_f32_kernel<128, 1>), grid, dim3(kThreads), 0, st, a, (int)n_kv);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || R == 1 || n_kv == 0) return e;
+  const size_t n4 = (size_t)a.P * a.hkv * head_dim / 4;
+  hipLaunchKernelGGL(kv_combine_f32_kernel, dim3((unsigned)((n4 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
+                     a, n4);
   return hipGetLastError();
+}
+
+int f32_kvsplit(long kv_tiles, long max_tiles, int group) {
+  // As bwd_bf16_kvsplit: key tile 0 sweeps every row (max_tiles 32-row steps
+  // of one kv head), and it would end the launch alone where that is over
+  // 10% more than a slot's average of the launch (two slots per CU, the
+  // query-outer role adding three quarters of kv_tiles).  Measured at
+  // P = 1000, Hq 32, Hkv 8: Phase C 417 us whole, 299 in three shares.  Share 0 goes to
+  // the outputs and the workspace holds group / 2 more (prefix_bwd_parts).
+  const double per_slot = 1.75 * (double)kv_tiles / 512;
+  if ((double)max_tiles <= 1.1 * per_slot) return 1;
+  const long r = std::min((long)std::ceil((double)max_tiles / per_slot), max_tiles / 8);
+  return (int)std::max(1L, std::min(r, 1L + group / 2));
 }
 
 }  // namespace spr

@@ -70,6 +70,8 @@ int bwd_bf16_kvsplit(long kv_tiles, long max_tiles, bool kv_alone, int slots = 5
 int bwd_bf16_block_q();
 int f32_block_q();
 int f32_block_k();
+// row shares of Phase C's key-outer role in fp32 storage (1 + group / 2 at most)
+int f32_kvsplit(long kv_tiles, long max_tiles, int group);
 
 // --- auxiliary kernels (kernels_aux.hip) ----------------------------------
 // dd[row * hq + h] = sum_d dO[row,h,d] * O[row,h,d] and

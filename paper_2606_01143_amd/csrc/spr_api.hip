@@ -325,8 +325,9 @@ WsLayout ws_layout(int op, const spr_dims* d, int32_t n_mb, int32_t max_len, int
     off = align_up(off + bytes, 256);
     return at;
   };
-  // the bf16 path writes dQ directly (query-outer kernel); the fp32 path
-  // accumulates it in fp32 and converts
+  // both storage types write dQ directly (query-outer role); only the atomic
+  // mode accumulates it in fp32 and converts.  fp32 storage keeps the
+  // accumulator's bytes: Phase C's row shares use them
   const bool f32 = d->dtype == SPR_F32;
   switch (op) {
     case SPR_OP_PREFIX_FWD:
@@ -687,11 +688,10 @@ spr_status spr_suffix_attn_bwd_accum(const spr_dims* dims, const void* k_p, cons
   all.push_back({ws, w.total, "ws", false});
   if ((st = check_aliasing({bufs[12], bufs[13]}, all)) != SPR_OK) return st;
 
-  const bool f32 = dims->dtype == SPR_F32;
   const bool aq = atomic_dq(dims);
   float* dd_s = at<float>(ws, w.dd_s);
   float* lse2_s = at<float>(ws, w.lse2_s);
-  float* dq_acc = (f32 || aq) ? at<float>(ws, w.dq_acc_s) : nullptr;
+  float* dq_acc = aq ? at<float>(ws, w.dq_acc_s) : nullptr;
   if ((st = hip_check(launch_row_dot(dims->dtype, do_s, o_s, total_len, total_len, nullptr, 0, (int)hq,
                                      (int)hd, dd_s, lse_s, lse2_s, stream), "row statistic")) != SPR_OK)
     return st;
@@ -900,13 +900,12 @@ spr_status prefix_bwd_parts(const spr_dims* dims, const void* q_p, const void* k
       return st;
     return ok();
   }
-  const bool f32 = dims->dtype == SPR_F32;
   // the whole Phase C adds dQ atomically from the key-outer blocks; the dQ
   // half alone keeps its query-outer role (fewer products without dK/dV)
   const bool aq = atomic_dq(dims) && want_dq && want_dkv;
   float* dd_p = at<float>(ws, w.dd_p);
   float* lse2_p = at<float>(ws, w.lse2_p);
-  float* dq_acc = (f32 || aq) && want_dq ? at<float>(ws, w.dq_acc_p) : nullptr;
+  float* dq_acc = aq ? at<float>(ws, w.dq_acc_p) : nullptr;
   if ((st = hip_check(launch_row_dot(dims->dtype, do_p, o_p, (int)P, (int)P, nullptr, 0, (int)hq, (int)hd,
                                      dd_p, lse_p, lse2_p, stream), "row statistic")) != SPR_OK)
     return st;
@@ -936,6 +935,15 @@ spr_status prefix_bwd_parts(const spr_dims* dims, const void* q_p, const void* k
     if (a.kv_rsplit > 1) {
       a.part_dk = at<float>(ws, w.part_dk);
       a.part_dv = at<float>(ws, w.part_dv);
+    }
+    if (dims->dtype == SPR_F32) {
+      // the workspace's [P, Hq, d] fp32 region holds dK and dV of
+      // Hq / Hkv / 2 row shares beyond the first
+      const long g = dims->num_q_heads / dims->num_kv_heads, bk = f32_block_k();
+      a.kv_rsplit = f32_kvsplit(causal_steps(dims->prefix_len, g, bk) * dims->num_kv_heads,
+                                g * tiles(dims->prefix_len, 32), (int)g);
+      a.part_dk = at<float>(ws, w.dq_acc_p);
+      a.part_dv = a.part_dk + (size_t)(a.kv_rsplit - 1) * P * hkv * hd;
     }
   }
   if (wide) {
@@ -1022,12 +1030,11 @@ spr_status spr_dense_recompute_baseline(
   if ((st = check_ws(w, ws, ws_bytes)) != SPR_OK) return st;
   float* dd_p = at<float>(ws, w.dd_p);
   float* dq_acc_p = at<float>(ws, w.dq_acc_p);
-  const bool f32 = dims->dtype == SPR_F32;
   float* dd_s = at<float>(ws, w.dd_s);
   float* lse2_p = at<float>(ws, w.lse2_p);
   float* lse2_s = at<float>(ws, w.lse2_s);
   const bool aq = atomic_dq(dims);
-  float* dq_acc_s = (f32 || aq) ? at<float>(ws, w.dq_acc_s) : nullptr;
+  float* dq_acc_s = aq ? at<float>(ws, w.dq_acc_s) : nullptr;
   float* dk_acc = at<float>(ws, w.dk_acc_p);
   float* dv_acc = at<float>(ws, w.dv_acc_p);
   const float scale = eff_scale(dims);
