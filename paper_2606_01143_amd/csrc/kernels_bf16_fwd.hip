@@ -68,9 +68,26 @@ __device__ __forceinline__ RowBlock decode_row_block(const AttnArgs& a, int ntx)
 // K/V tile that waves 0-3 load, no key splits.  Both keep the 64 KB of
 // double-buffered tiles, so only the twelve-wave form holds three waves on
 // every SIMD, which needs the loop to fit in 168 registers.
-template <int D, bool WIDE>
+//
+// PACK (four waves, suffix rows only): the 128 rows of a workgroup are
+// consecutive (token, q head) pairs of one kv head, row x = token x / G, head
+// x % G.  A one-head row tile of a short suffix is mostly padding; the G
+// heads of a kv head read the same K/V, so together they fill it.  Where the
+// launch has too few such tiles for the chip, its keys are split by segment
+// (n_split > 1): blocks over the rows of the whole microbatch, suffixes side
+// by side, take n_split - 1 ranges of the prefix keys (every row sees all of
+// them, so the prefix is swept once for all suffixes), and blocks over one
+// suffix's rows take its own keys as the last split.  A row's result does
+// not depend on the suffixes beside it: its key tiles start at the same keys
+// wherever it lies.
+// Measured at Hq 32, Hkv 8, d 128, P = 8191 with suffixes of 1, 24, 7 and 16
+// tokens: 69 us per call in one-head tiles, 32 us with packed rows per suffix,
+// 25 us with the shared prefix ranges.
+enum FwdForm { kFwdRows, kFwdWide, kFwdPack };
+template <int D, FwdForm FORM>
 __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D>::ELEMS],
-                                         bf16 (&Vs)[2][Tile<D>::ELEMS]) {
+                                         bf16 (&Vs)[2][Tile<D>::ELEMS], const int all_tiles = 0) {
+  constexpr bool WIDE = FORM == kFwdWide, PACK = FORM == kFwdPack;
   constexpr int NS = D / 16;   // k-steps over d for S^T
   constexpr int NDB = D / 32;  // 32-wide d blocks of O^T
   constexpr int BK = kTileRows;
@@ -84,6 +101,7 @@ __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D
   // ---- which BQ query rows: prefix rows, or rows of suffix seq_base + z
   const int ntx = a.n_prefix_q_tiles + a.n_suffix_q_tiles;
   int hq, hk;
+  bool shared = false;  // PACK: rows of the whole microbatch on a prefix key range
   RowBlock blk;
   if constexpr (WIDE) {
     // block b -> (kv head b % Hkv, group of four q heads, 96-row tile,
@@ -98,6 +116,24 @@ __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D
     blk.z = b / ntx;
     blk.split = 0;
     hq = hk * G + 4 * hg + (w & 3);
+  } else if constexpr (PACK) {
+    // block b -> (kv head b % Hkv, prefix key range, 128-row tile of the
+    // microbatch), then (kv head, 128-row tile, suffix)
+    int b = blockIdx.x;
+    hk = b % a.hkv;
+    b /= a.hkv;
+    shared = b < all_tiles * (a.n_split - 1);
+    if (shared) {
+      blk.split = b % (a.n_split - 1);
+      blk.tile = b / (a.n_split - 1);
+      blk.z = 0;
+    } else {
+      b -= all_tiles * (a.n_split - 1);
+      blk.split = a.n_split - 1;
+      blk.tile = ntx - 1 - b % ntx;
+      blk.z = b / ntx;
+    }
+    hq = 0;  // per lane, below
   } else {
     blk = decode_row_block(a, ntx);
     hq = blk.hq;
@@ -106,7 +142,16 @@ __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D
   const int seq = a.seq_base + blk.z;
   bool prefix_rows;
   int lp0, seg_len, row_base;
-  if (blk.tile < a.n_prefix_q_tiles) {
+  const int G = PACK ? a.hq / a.hkv : 1;  // rows per token
+  if constexpr (PACK) {
+    prefix_rows = false;
+    lp0 = blk.tile * BQ;
+    const SegRows sg = shared ? suffix_span(a.cu, a.seq_base, a.seq_base + a.n_seq, a.total_len)
+                              : suffix_rows(a.cu, seq, a.total_len);
+    row_base = sg.base;
+    seg_len = sg.len * G;
+    hq = hk * G + min(lp0 + 32 * w + r, seg_len - 1) % G;
+  } else if (blk.tile < a.n_prefix_q_tiles) {
     prefix_rows = true;
     lp0 = blk.tile * BQ;
     seg_len = a.P;
@@ -122,7 +167,10 @@ __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D
   const int wave_lp0 = lp0 + 32 * (WIDE ? w >> 2 : w);  // first row of this wave
   const int row_lp = wave_lp0 + r;    // this lane's query row (segment-local)
   const bool row_valid = row_lp < seg_len;
-  const int my_lp = row_valid ? row_lp : seg_len - 1;  // rows past the end recompute the last one
+  // rows past the end recompute the last one (PACK: the token of the row)
+  const int my_lp = (row_valid ? row_lp : seg_len - 1) / G;
+  // first and last token of the wave
+  const int wave_first = wave_lp0 / G, wave_last = (wave_lp0 + 31) / G;
 
   // Q as the B operand of S^T = K Q^T: slot (h, j) of k-step s is d = 16 s + 8 h + j
   bf16x8 qf[NS];
@@ -140,13 +188,15 @@ __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D
   float m = -INFINITY, l = 0.f;  // running max (log2 domain) and sum of row my_lp
 
   // key tiles: prefix keys first (causal for prefix rows), then own suffix keys
-  const int last_lp = min(lp0 + BQ, seg_len) - 1;
-  const int nkeys0 = prefix_rows ? min(a.P, last_lp + 1) : a.P;
-  const int nkeys1 = prefix_rows ? 0 : last_lp + 1;
+  const int last_lp = (min(lp0 + BQ, seg_len) - 1) / G;
+  const bool own = PACK && a.n_split > 1 && !shared;  // own suffix keys only
+  const int nkeys0 = prefix_rows ? min(a.P, last_lp + 1) : own ? 0 : a.P;
+  const int nkeys1 = prefix_rows || shared ? 0 : last_lp + 1;
   const int nt0 = (nkeys0 + BK - 1) / BK, nt1 = (nkeys1 + BK - 1) / BK;
   // this block's contiguous share of the key tiles
-  const int t_begin = (int)((long)(nt0 + nt1) * blk.split / a.n_split);
-  const int t_end = (int)((long)(nt0 + nt1) * (blk.split + 1) / a.n_split);
+  const int share = own ? 0 : blk.split, shares = PACK ? (shared ? a.n_split - 1 : 1) : a.n_split;
+  const int t_begin = (int)((long)(nt0 + nt1) * share / shares);
+  const int t_end = (int)((long)(nt0 + nt1) * (share + 1) / shares);
 
   const bf16 *k_p = in_sgpr((const bf16*)a.k_p), *k_s = in_sgpr((const bf16*)a.k_s);
   const bf16 *v_p = in_sgpr((const bf16*)a.v_p), *v_s = in_sgpr((const bf16*)a.v_s);
@@ -167,7 +217,8 @@ __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D
     const int k0 = (seg == 0 ? t : t - nt0) * BK;
     const int nk = min(BK, (seg == 0 ? nkeys0 : nkeys1) - k0);
     const bool causal = (seg == 0) == prefix_rows;  // keys of the row's own segment
-    if (causal && k0 > wave_lp0 + 31) return;       // no row of this wave sees the tile
+    if (PACK && wave_lp0 >= seg_len) return;        // no row of this wave at all
+    if (causal && k0 > wave_last) return;           // no row of this wave sees the tile
     // S^T = K Q^T ; st[kb][i] = S^T[key k0 + 32 kb + c_row0(i) + 4 h][row my_lp]
     f32x16 st[2] = {zero16(), zero16()};
 #pragma unroll
@@ -176,7 +227,7 @@ __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D
       for (int kb = 0; kb < 2; ++kb) st[kb] = mfma32(row_frag<D>(Kc, fo, 32 * kb, s), qf[s], st[kb]);
     sched_reads_ahead<2 * NS, 1, 4>();
 #define SC(e) st[(e) >> 4][(e) & 15]
-    if (nk < BK || (causal && k0 + BK - 1 > wave_lp0)) {  // partial or diagonal tile
+    if (nk < BK || (causal && k0 + BK - 1 > wave_first)) {  // partial or diagonal tile
       // keys kk = 32 (e / 16) + c_row0(e % 16) + 4 h are visible iff kk < lim
       int lp = my_lp;  // recomputed in the twelve-wave form (registers)
       if constexpr (WIDE)
@@ -286,14 +337,21 @@ template <int D>
 __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) bf16 Ks[2][Tile<D>::ELEMS];
   __shared__ __attribute__((aligned(1024))) bf16 Vs[2][Tile<D>::ELEMS];
-  fwd_body<D, false>(a, Ks, Vs);
+  fwd_body<D, kFwdRows>(a, Ks, Vs);
 }
 
 template <int D>
 __global__ __launch_bounds__(3 * kThreads, 1) void fwd_wide_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) bf16 Ks[2][Tile<D>::ELEMS];
   __shared__ __attribute__((aligned(1024))) bf16 Vs[2][Tile<D>::ELEMS];
-  fwd_body<D, true>(a, Ks, Vs);
+  fwd_body<D, kFwdWide>(a, Ks, Vs);
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads, 2) void fwd_pack_kernel(AttnArgs a, int all_tiles) {
+  __shared__ __attribute__((aligned(1024))) bf16 Ks[2][Tile<D>::ELEMS];
+  __shared__ __attribute__((aligned(1024))) bf16 Vs[2][Tile<D>::ELEMS];
+  fwd_body<D, kFwdPack>(a, Ks, Vs, all_tiles);
 }
 
 // Merge of the n_split partial outputs of every (suffix row, q head):
@@ -307,19 +365,43 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(AttnArgs a) {
   const int c = (int)(idx % TPR);
   const long nrh = (long)a.total_len * a.hq;
   if (rh >= nrh) return;
-  float mx = -INFINITY;
-  for (int j = 0; j < a.n_split; ++j) mx = fmaxf(mx, a.part_lse[(size_t)j * nrh + rh]);
-  float sum = 0.f;
+  // Four splits' partials are loaded together (the launch is bound by their
+  // latency: 16 splits of 48 rows 10.0 us one by one, 22 splits 5.4 us so), against a running maximum.
+  constexpr int kB = 4;
+  float mx = -INFINITY, sum = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int j = 0; j < a.n_split; ++j) {
-    const float lj = a.part_lse[(size_t)j * nrh + rh];
-    const float wj = lj == -INFINITY ? 0.f : exp2f(lj - mx);
-    const float4 oj = *(const float4*)(a.part_o + ((size_t)j * nrh + rh) * D + 4 * c);
-    sum += wj;
-    acc.x += wj * oj.x;
-    acc.y += wj * oj.y;
-    acc.z += wj * oj.z;
-    acc.w += wj * oj.w;
+  for (int j0 = 0; j0 < a.n_split; j0 += kB) {
+    float l[kB];
+    float4 o[kB];
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      const size_t row = (size_t)min(j0 + i, a.n_split - 1) * nrh + rh;
+      l[i] = a.part_lse[row];
+      o[i] = *(const float4*)(a.part_o + row * D + 4 * c);
+    }
+    float mn = mx;
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      if (j0 + i >= a.n_split) l[i] = -INFINITY;
+      mn = fmaxf(mn, l[i]);
+    }
+    const float mu = mn == -INFINITY ? 0.f : mn;
+    const float corr = exp2f(mx - mu);
+    sum *= corr;
+    acc.x *= corr;
+    acc.y *= corr;
+    acc.z *= corr;
+    acc.w *= corr;
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+      const float wj = exp2f(l[i] - mu);  // 0 for a range with no visible key
+      sum += wj;
+      acc.x += wj * o[i].x;
+      acc.y += wj * o[i].y;
+      acc.z += wj * o[i].z;
+      acc.w += wj * o[i].w;
+    }
+    mx = mn;
   }
   const float inv = 1.f / sum;
   const bf16x4 v = {(bf16)(acc.x * inv), (bf16)(acc.y * inv), (bf16)(acc.z * inv), (bf16)(acc.w * inv)};
@@ -327,16 +409,10 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(AttnArgs a) {
   if (c == 0) a.lse_s[rh] = (mx + log2f(sum)) * kLn2;
 }
 
-hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int n_z, hipStream_t st) {
-  const long nb = (long)(a.n_prefix_q_tiles + a.n_suffix_q_tiles) * a.hq * n_z * a.n_split;
-  if (nb == 0) return hipSuccess;
-  ProfileScope ps("fwd_bf16", st);
-  if (head_dim == 64)
-    hipLaunchKernelGGL(fwd_bf16_kernel<64>, dim3((unsigned)nb), dim3(kThreads), 0, st, a);
-  else
-    hipLaunchKernelGGL(fwd_bf16_kernel<128>, dim3((unsigned)nb), dim3(kThreads), 0, st, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.n_split <= 1) return e;
+namespace {
+// the key splits' partials merged
+hipError_t launch_fwd_combine(const AttnArgs& a, int head_dim, hipStream_t st) {
+  if (a.n_split <= 1) return hipSuccess;
   const long threads = (long)a.total_len * a.hq * (head_dim / 4);
   const unsigned cb = (unsigned)((threads + 255) / 256);
   ProfileScope pc("fwd_combine", st);
@@ -345,6 +421,40 @@ hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int n_z, hipStream_t
   else
     hipLaunchKernelGGL(fwd_combine_kernel<128>, dim3(cb), dim3(256), 0, st, a);
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int n_z, hipStream_t st) {
+  const long nb = (long)(a.n_prefix_q_tiles + a.n_suffix_q_tiles) * a.hq * n_z * a.n_split;
+  if (nb == 0) return hipSuccess;
+  {
+    ProfileScope ps("fwd_bf16", st);
+    if (head_dim == 64)
+      hipLaunchKernelGGL(fwd_bf16_kernel<64>, dim3((unsigned)nb), dim3(kThreads), 0, st, a);
+    else
+      hipLaunchKernelGGL(fwd_bf16_kernel<128>, dim3((unsigned)nb), dim3(kThreads), 0, st, a);
+  }
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_fwd_combine(a, head_dim, st);
+}
+
+// The suffix forward in its packed-row form: a.n_suffix_q_tiles counts
+// 128-row tiles of a suffix's (token, q head of a kv head) pairs.
+hipError_t launch_fwd_bf16_pack(const AttnArgs& a, int head_dim, int n_z, hipStream_t st) {
+  if (a.n_prefix_q_tiles) return hipErrorInvalidValue;
+  const long rows = (long)a.total_len * (a.hq / a.hkv);
+  const int all = a.n_split > 1 ? (int)((rows + kFwdBQ - 1) / kFwdBQ) : 0;
+  const long nb = ((long)all * (a.n_split - 1) + (long)a.n_suffix_q_tiles * n_z) * a.hkv;
+  if (nb == 0) return hipSuccess;
+  {
+    ProfileScope ps("fwd_bf16", st);
+    if (head_dim == 64)
+      hipLaunchKernelGGL(fwd_pack_kernel<64>, dim3((unsigned)nb), dim3(kThreads), 0, st, a, all);
+    else
+      hipLaunchKernelGGL(fwd_pack_kernel<128>, dim3((unsigned)nb), dim3(kThreads), 0, st, a, all);
+  }
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_fwd_combine(a, head_dim, st);
 }
 
 // The forward in its twelve-wave form: a.n_prefix_q_tiles and
@@ -372,6 +482,25 @@ int fwd_bf16_split(int n_row_blocks, int prefix_len) {
   int ns = (512 + n_row_blocks - 1) / n_row_blocks;
   ns = std::min(ns, std::max(1, prefix_len / (4 * kTileRows)));
   return std::max(1, std::min(ns, 16));
+}
+
+long fwd_bf16_pack_tiles(int hq, int hkv, int max_len) {
+  const long g = hq / hkv;
+  const long packed = (max_len * g + kFwdBQ - 1) / kFwdBQ;
+  const long rows = ((max_len + kFwdBQ - 1) / kFwdBQ) * g;
+  return 4 * packed <= 3 * rows ? packed : 0;
+}
+
+int fwd_bf16_pack_split(int hq, int hkv, int n_mb, int max_len, int prefix_len) {
+  // One split (the suffix's own keys with the prefix) where the suffixes'
+  // tiles give every CU two workgroups; else the prefix keys in as many
+  // ranges of at least four 64-key tiles as make about two workgroups per
+  // CU, plus one.  The partials then stay below 512 tiles of fp32 rows.
+  const long tiles = fwd_bf16_pack_tiles(hq, hkv, max_len) * n_mb * hkv;
+  if (tiles >= 512 || prefix_len < 4 * kTileRows) return 1;
+  const long all = ((long)n_mb * max_len * (hq / hkv) + kFwdBQ - 1) / kFwdBQ * hkv;
+  const long ns = std::min(512 / all, (long)prefix_len / (4 * kTileRows));
+  return (int)std::max(1L, std::min(ns, 32L)) + 1;
 }
 
 }  // namespace spr

@@ -49,6 +49,7 @@ hipError_t launch_bwd_f32(const AttnArgs& a, int head_dim, int n_qz, hipStream_t
 hipError_t launch_fwd_bf16(const AttnArgs& a, int head_dim, int n_z, hipStream_t st);
 hipError_t launch_fwd_bf16_wide(const AttnArgs& a, int head_dim, int n_z, hipStream_t st);
 int fwd_bf16_wide_block_q();
+hipError_t launch_fwd_bf16_pack(const AttnArgs& a, int head_dim, int n_z, hipStream_t st);
 hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, int n_qz, bool deterministic,
                            hipStream_t st);
 // Row-tile sizes the launchers expect in AttnArgs (q tiles / k tiles).
@@ -56,6 +57,12 @@ int fwd_bf16_block_q();
 // key splits of the bf16 suffix forward for n_row_blocks (row tile, q head,
 // suffix) blocks and a prefix of prefix_len keys
 int fwd_bf16_split(int n_row_blocks, int prefix_len);
+// row tiles per suffix and kv head of the suffix forward's packed-row form,
+// taken where that is at most 3/4 of the one-head form's (short suffixes, or
+// lengths just past a multiple of 128); 0: the one-head form
+long fwd_bf16_pack_tiles(int hq, int hkv, int max_len);
+// its key splits: 1, or the prefix key ranges plus one for the suffixes' own
+int fwd_bf16_pack_split(int hq, int hkv, int n_mb, int max_len, int prefix_len);
 int bwd_bf16_block_k();
 // key-outer role alone with six wave pairs (192 keys) per workgroup, one
 // workgroup per CU, for the prefix backward of long prefixes (default mode)

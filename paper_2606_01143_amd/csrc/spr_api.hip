@@ -144,6 +144,8 @@ AttnArgs base_args(const spr_dims* d) {
 // key splits of the suffix forward (bf16 path only), see fwd_bf16_split
 int suffix_fwd_splits(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   if (d->dtype != SPR_BF16) return 1;
+  if (fwd_bf16_pack_tiles(d->num_q_heads, d->num_kv_heads, max_len) > 0)
+    return fwd_bf16_pack_split(d->num_q_heads, d->num_kv_heads, n_mb, max_len, d->prefix_len);
   const int nrb = tiles(max_len, fwd_bf16_block_q()) * d->num_q_heads * n_mb;
   return fwd_bf16_split(nrb, d->prefix_len);
 }
@@ -291,6 +293,10 @@ hipError_t launch_forward(const spr_dims* d, AttnArgs a, bool prefix, int32_t ma
     a.n_prefix_q_tiles = (int)pw;
     a.n_suffix_q_tiles = (int)sw;
     return launch_fwd_bf16_wide(a, d->head_dim, n_z, st);
+  }
+  if (!prefix && d->dtype == SPR_BF16) {
+    a.n_suffix_q_tiles = (int)fwd_bf16_pack_tiles(d->num_q_heads, d->num_kv_heads, max_len);
+    if (a.n_suffix_q_tiles > 0) return launch_fwd_bf16_pack(a, d->head_dim, n_z, st);
   }
   const int q = block_q(d->dtype);
   a.n_prefix_q_tiles = prefix ? tiles(d->prefix_len, q) : 0;
