@@ -110,24 +110,86 @@ __global__ __launch_bounds__(kRowThreads) void rmsnorm_bwd_kernel(const bf16* __
   }
 }
 
-// one workgroup per token; thread (head, j) rotates the pair (j, j + d/2)
-__global__ __launch_bounds__(kRowThreads) void rope_kernel(const bf16* __restrict__ x, bf16* __restrict__ y,
-                                                           int heads, int d, int pos0, double theta, float sign) {
+// cos and sin of token position pos at frequency theta^(-2j/d): angle in
+// fp64, reduced to [-pi, pi] before the fp32 sine and cosine
+__device__ __forceinline__ float2 rope_angle(double pos, double freq, float sign) {
+  const double ang = remainder(pos * freq, 2.0 * M_PI);
+  float sn, cs;
+  sincosf((float)ang, &sn, &cs);
+  return make_float2(cs, sn * sign);
+}
+
+// head dims that are a multiple of 16 (16-byte chunks of both halves): one
+// workgroup per kRopeTokens tokens.  The fp64 power, reduction and sincos of
+// a pair (token, j) cost far more than the memory the pair moves, and are the
+// same for every head, so each is computed once into LDS and the heads
+// stream past it; the first kRopeAhead chunk pairs of a thread are loaded
+// before the angles are formed.  Measured on 4096 tokens x 32 heads x 128
+// (67 MB): one angle per (token, head, j) 87 us, this form 14.4 us
+// (4.7 TB/s).
+constexpr int kRopeTokens = 4, kRopeAhead = 4, kRopeMaxHalf = 128;
+
+__global__ __launch_bounds__(kRowThreads) void rope_shared_kernel(const bf16* x, bf16* y, long tokens, int heads,
+                                                                  int d, int pos0, double theta, float sign) {
+  __shared__ float2 cs[kRopeTokens][kRopeMaxHalf];
+  const int half = d / 2, cpr = half / 8;  // 16-byte chunks per half row
+  const long t0 = (long)blockIdx.x * kRopeTokens;
+  const int nt = (int)min((long)kRopeTokens, tokens - t0);
+  const int n = nt * heads * cpr;
+  const bf16* xb = x + t0 * heads * d;
+  bf16* yb = y + t0 * heads * d;
+  // chunk i: row (token, head) i / cpr of this workgroup, columns 8 (i % cpr)
+  auto at = [&](int i) { return (long)(i / cpr) * d + 8 * (i % cpr); };
+  bf16x8 lo[kRopeAhead], hi[kRopeAhead];
+#pragma unroll
+  for (int q = 0; q < kRopeAhead; ++q) {
+    const int i = threadIdx.x + q * kRowThreads;
+    if (i < n) {
+      lo[q] = *(const bf16x8*)(xb + at(i));
+      hi[q] = *(const bf16x8*)(xb + at(i) + half);
+    }
+  }
+  for (int i = threadIdx.x; i < nt * half; i += kRowThreads) {
+    const int j = i % half;
+    const double freq = pow(theta, -2.0 * (double)j / (double)d);
+    cs[i / half][j] = rope_angle((double)(pos0 + t0 + i / half), freq, sign);
+  }
+  __syncthreads();
+  auto rotate = [&](int i, const bf16x8& a, const bf16x8& b) {
+    const float2* c = &cs[i / cpr / heads][8 * (i % cpr)];
+    bf16x8 oa, ob;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      oa[k] = (bf16)((float)a[k] * c[k].x - (float)b[k] * c[k].y);
+      ob[k] = (bf16)((float)b[k] * c[k].x + (float)a[k] * c[k].y);
+    }
+    *(bf16x8*)(yb + at(i)) = oa;
+    *(bf16x8*)(yb + at(i) + half) = ob;
+  };
+#pragma unroll
+  for (int q = 0; q < kRopeAhead; ++q) {
+    const int i = threadIdx.x + q * kRowThreads;
+    if (i < n) rotate(i, lo[q], hi[q]);
+  }
+  for (int i = threadIdx.x + kRopeAhead * kRowThreads; i < n; i += kRowThreads) {
+    const bf16x8 a = *(const bf16x8*)(xb + at(i)), b = *(const bf16x8*)(xb + at(i) + half);
+    rotate(i, a, b);
+  }
+}
+
+// any even head dim: one workgroup per token; thread (head, j) rotates the
+// pair (j, j + d/2)
+__global__ __launch_bounds__(kRowThreads) void rope_kernel(const bf16* x, bf16* y, int heads, int d, int pos0,
+                                                           double theta, float sign) {
   const long t = blockIdx.x;
   const int half = d / 2;
-  const double pos = (double)(pos0 + t);
   for (int i = threadIdx.x; i < heads * half; i += kRowThreads) {
     const int h = i / half, j = i % half;
-    // angle in fp64, reduced to [-pi, pi] before the fp32 sine and cosine
-    double ang = pos * pow(theta, -2.0 * (double)j / (double)d);
-    ang = remainder(ang, 2.0 * M_PI);
-    float sn, cs;
-    sincosf((float)ang, &sn, &cs);
-    sn *= sign;
+    const float2 c = rope_angle((double)(pos0 + t), pow(theta, -2.0 * (double)j / (double)d), sign);
     const long base = (t * heads + h) * d;
     const float a = (float)x[base + j], b = (float)x[base + j + half];
-    y[base + j] = (bf16)(a * cs - b * sn);
-    y[base + j + half] = (bf16)(b * cs + a * sn);
+    y[base + j] = (bf16)(a * c.x - b * c.y);
+    y[base + j + half] = (bf16)(b * c.x + a * c.y);
   }
 }
 
@@ -184,8 +246,13 @@ hipError_t launch_rope(int tokens, int heads, int d, int pos0, double theta, con
                        hipStream_t st) {
   if (tokens == 0) return hipSuccess;
   ProfileScope ps(inverse ? "rope_bwd" : "rope_fwd", st);
-  hipLaunchKernelGGL(rope_kernel, dim3(tokens), dim3(kRowThreads), 0, st, (const bf16*)x, (bf16*)y, heads, d, pos0,
-                     theta, inverse ? -1.f : 1.f);
+  const float sign = inverse ? -1.f : 1.f;
+  if (d % 16 == 0 && d / 2 <= kRopeMaxHalf)
+    hipLaunchKernelGGL(rope_shared_kernel, dim3((tokens + kRopeTokens - 1) / kRopeTokens), dim3(kRowThreads), 0, st,
+                       (const bf16*)x, (bf16*)y, (long)tokens, heads, d, pos0, theta, sign);
+  else
+    hipLaunchKernelGGL(rope_kernel, dim3(tokens), dim3(kRowThreads), 0, st, (const bf16*)x, (bf16*)y, heads, d, pos0,
+                       theta, sign);
   return hipGetLastError();
 }
 
