@@ -4,9 +4,13 @@
 // probability gradient.
 //
 // Everything here streams the [tokens, E] probability matrix once (HBM
-// bound).  Reductions run in a fixed order so that results are bitwise
-// reproducible: per-block partials in fp64 / int64, then one pass that adds
-// the partials of all blocks in block order into the statistics.
+// bound).  Floating-point reductions run in a fixed order, so results are
+// bitwise reproducible.  Token sets of up to kMoeDirectTokens (a suffix
+// microbatch, a prompt) take one launch, whose time is a few memory round
+// trips: blocks that each own four experts sum their mass over every token,
+// beside blocks that count a slice of the selected ids (integer adds, exact
+// in any order).  Larger ones write per-block partials in fp64 / int64, and
+// one pass adds the partials of all blocks in block order.
 #include <stdint.h>
 
 #include <algorithm>
@@ -22,6 +26,106 @@ __device__ __forceinline__ long long token_mult(int u, int mult, const int* mu) 
   return mu != nullptr ? (long long)mu[u] : (long long)mult;
 }
 }  // namespace
+
+// One launch.  Blocks 0 .. E/4 - 1: the mass of experts 4 q .. 4 q + 3, thread
+// t summing tokens t, t + 512, ... in order (eight loads in flight), then a
+// fixed tree over the threads.  The other blocks: kMoeCountPairs selected ids
+// each into an LDS histogram, added to the statistics with integer atomics,
+// and the multiplicity total of the tokens those ids belong to.
+//
+// Measured on one suffix microbatch (1000 tokens, E = 128, top-8): partials
+// 5.1 us + reduction 3.3 us and the gap between them, this launch 4.7 us;
+// 8192 tokens 7.9 us.  A mass block reads 16 bytes of every row, so the
+// cache lines are fetched by several blocks: the blocks of one XCD (b % 8)
+// take neighbouring experts, and each XCD's L2 fetches a line once.
+constexpr int kMoeDirectThreads = 512;
+constexpr int kMoeCountPairs = 2048;
+constexpr int kMoeDirectTokens = 16384;
+constexpr long kMoeDirectPairs = 262144;  // 128 counting blocks' integer atomics
+
+__global__ __launch_bounds__(kMoeDirectThreads) void moe_direct_kernel(const float* __restrict__ p,
+                                                                       const int* __restrict__ r, int n, int E,
+                                                                       int k, int mult, const int* __restrict__ mu,
+                                                                       unsigned char* __restrict__ stats) {
+  const int tid = threadIdx.x, cols = E / 4;
+  unsigned long long* count = (unsigned long long*)stats;
+  double* mass = (double*)(stats + 8 * (size_t)E);
+  unsigned long long* total = (unsigned long long*)(stats + 16 * (size_t)E);  // then the invalid ids
+  if ((int)blockIdx.x < cols) {
+    const int b = blockIdx.x;
+    const int q = cols % 8 == 0 ? (b % 8) * (cols / 8) + b / 8 : b;
+    constexpr int kRows = 8, kWaves = kMoeDirectThreads / 64;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int u0 = tid; u0 < n; u0 += kRows * kMoeDirectThreads) {
+      float4 v[kRows];
+      double m[kRows];
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) {
+        const int u = u0 + i * kMoeDirectThreads;
+        const bool in = u < n;
+        v[i] = in ? *(const float4*)(p + (size_t)u * E + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+        m[i] = in ? (double)token_mult(u, mult, mu) : 0.0;
+      }
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) {
+        a[0] = fma(m[i], (double)v[i].x, a[0]);
+        a[1] = fma(m[i], (double)v[i].y, a[1]);
+        a[2] = fma(m[i], (double)v[i].z, a[2]);
+        a[3] = fma(m[i], (double)v[i].w, a[3]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) a[j] += __shfl_xor(a[j], o);
+    __shared__ double red[kWaves][4];
+    if ((tid & 63) == 0)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) red[tid >> 6][j] = a[j];
+    __syncthreads();
+    if (tid < 4) {
+      double s = 0.0;
+      for (int w = 0; w < kWaves; ++w) s += red[w][tid];
+      mass[4 * q + tid] += s;
+    }
+    return;
+  }
+  // ids [i0, i1), tokens [u0, u1): the last block of a token set ends at n
+  __shared__ unsigned long long hist[1024];
+  __shared__ unsigned long long tot, inval;
+  const int c = blockIdx.x - cols;
+  const long pairs = (long)n * k, i0 = (long)c * kMoeCountPairs, i1 = min(pairs, i0 + kMoeCountPairs);
+  for (int e = tid; e < E; e += kMoeDirectThreads) hist[e] = 0;
+  if (tid == 0) tot = inval = 0;
+  __syncthreads();
+  constexpr int kPer = kMoeCountPairs / kMoeDirectThreads;
+  int id[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const long i = i0 + tid + j * kMoeDirectThreads;
+    id[j] = i < i1 ? r[i] : 0;
+  }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const long i = i0 + tid + j * kMoeDirectThreads;
+    if (i < i1) {
+      const long u = i / k;
+      const unsigned long long m = (unsigned long long)token_mult((int)u, mult, mu);
+      if (id[j] >= 0 && id[j] < E)
+        atomicAdd(&hist[id[j]], m);
+      else
+        atomicAdd(&inval, 1ull);
+      if (u * k == i) atomicAdd(&tot, m);  // once per token, at its first id
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < E; e += kMoeDirectThreads)
+    if (hist[e] != 0) atomicAdd(&count[e], hist[e]);
+  if (tid == 0) {
+    if (tot != 0) atomicAdd(&total[0], tot);
+    if (inval != 0) atomicAdd(&total[1], inval);
+  }
+}
 
 // Block b takes tokens [b chunk, (b + 1) chunk).  Counts go through an LDS
 // histogram (64-bit integer adds, exact); the probability mass is summed per
@@ -216,6 +320,13 @@ hipError_t launch_moe_accumulate(const float* p, const int* r, int n, int E, int
                                  const int* mu, void* stats, void* ws, hipStream_t st) {
   const int nb = moe_blocks(n);
   if (nb == 0) return hipSuccess;
+  if (n <= kMoeDirectTokens && (long)n * k <= kMoeDirectPairs) {
+    const long counters = ((long)n * k + kMoeCountPairs - 1) / kMoeCountPairs;
+    ProfileScope ps("moe_partial", st);
+    hipLaunchKernelGGL(moe_direct_kernel, dim3((unsigned)(E / 4 + counters)), dim3(kMoeDirectThreads), 0, st, p, r, n,
+                       E, k, mult, mu, (unsigned char*)stats);
+    return hipGetLastError();
+  }
   const int chunk = (n + nb - 1) / nb;
   double* part_mass = (double*)ws;
   long long* part_count = (long long*)((unsigned char*)ws + (size_t)nb * E * 8);
