@@ -148,6 +148,7 @@ class DeviceGroup:
             self.ws = torch.empty(max(need, 256), device=self.device, dtype=torch.uint8)
         self.ws_fwd = torch.empty(need_f, device=self.device, dtype=torch.uint8)
         self._side = None  # suffix forward stream, made on first use
+        self._events: List[torch.cuda.Event] = []  # of the overlapped order, re-recorded by each run
 
     # ------------------------------------------------------------------
     def default_microbatches(self) -> List[Tuple[int, int]]:
@@ -284,19 +285,20 @@ class DeviceGroup:
         s_f = self._side
         with torch.cuda.stream(main):
             self.prepare(mbs)  # any cu_seqlens upload is ordered before `start`
-        start = torch.cuda.Event()
+        # one event per suffix forward and one for the start; a wait holds the
+        # record it was issued after, so the next run may record them again
+        while len(self._events) <= len(mbs):
+            self._events.append(torch.cuda.Event())
+        start = self._events[-1]
         start.record(main)
         B.gkv_cache_zero(self.dims, self.gk, self.gv, main)
         # suffix forwards in order on the side stream, one event each
         s_f.wait_event(start)
-        fwd_done = []
-        for a, b in mbs:
+        for (a, b), e in zip(mbs, self._events):
             self._suffix_fwd(a, b, self.ws_fwd, s_f)
-            e = torch.cuda.Event()
             e.record(s_f)
-            fwd_done.append(e)
         # backwards in microbatch order on the caller's stream
-        for (a, b), e in zip(mbs, fwd_done):
+        for (a, b), e in zip(mbs, self._events):
             main.wait_event(e)
             self._suffix_bwd(a, b, main)
         # Phase A, then Phase C (only Phase C reads Phase A's outputs)
