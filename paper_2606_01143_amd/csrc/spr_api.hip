@@ -144,10 +144,22 @@ AttnArgs base_args(const spr_dims* d) {
 // key splits of the suffix forward (bf16 path only), see fwd_bf16_split
 int suffix_fwd_splits(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   if (d->dtype != SPR_BF16) return 1;
-  if (fwd_bf16_pack_tiles(d->num_q_heads, d->num_kv_heads, max_len) > 0)
-    return fwd_bf16_pack_split(d->num_q_heads, d->num_kv_heads, n_mb, max_len, d->prefix_len);
   const int nrb = tiles(max_len, fwd_bf16_block_q()) * d->num_q_heads * n_mb;
   return fwd_bf16_split(nrb, d->prefix_len);
+}
+
+// the packed-row form's, where the suffix forward takes that form; 0: it doesn't
+int suffix_fwd_pack_splits(const spr_dims* d, int32_t n_mb, int32_t max_len) {
+  if (d->dtype != SPR_BF16 || fwd_bf16_pack_tiles(d->num_q_heads, d->num_kv_heads, max_len) == 0) return 0;
+  return fwd_bf16_pack_split(d->num_q_heads, d->num_kv_heads, n_mb, max_len, d->prefix_len);
+}
+// bytes of the suffix forward's partials (outputs, then LSE) for ns splits of
+// T rows
+size_t fwd_part_o_bytes(const spr_dims* d, size_t T, size_t ns) {
+  return ns <= 1 ? 0 : align_up(ns * T * d->num_q_heads * d->head_dim * 4, 256);
+}
+size_t fwd_part_bytes(const spr_dims* d, size_t T, size_t ns) {
+  return ns <= 1 ? 0 : fwd_part_o_bytes(d, T, ns) + align_up(ns * T * d->num_q_heads * 4, 256);
 }
 
 bool atomic_dq(const spr_dims* d);
@@ -319,6 +331,11 @@ struct WsLayout {
   size_t cu = 0, lens_c = 0, pq = 0, pk = 0, pv = 0, po = 0, plse = 0, pdo = 0;
   size_t pdq = 0, pdk = 0, pdv = 0, inner = 0, inner_bytes = 0;
   size_t total = 0;
+  // bytes a call insists on: less than total where the packed-row suffix
+  // forward would use more splits than its one-head form.  A workspace sized
+  // for other lengths (the longest suffix's, say) then still serves, with the
+  // splits that fit it.
+  size_t required = 0;
 };
 
 WsLayout ws_layout(int op, const spr_dims* d, int32_t n_mb, int32_t max_len, int32_t total_len) {
@@ -338,14 +355,10 @@ WsLayout ws_layout(int op, const spr_dims* d, int32_t n_mb, int32_t max_len, int
   switch (op) {
     case SPR_OP_PREFIX_FWD:
       break;
-    case SPR_OP_SUFFIX_FWD: {
-      const size_t ns = suffix_fwd_splits(d, n_mb, max_len);
-      if (ns > 1) {
-        w.part_o = take(ns * T * hq * hd * 4);
-        w.part_lse = take(ns * T * hq * 4);
-      }
-      break;
-    }
+    case SPR_OP_SUFFIX_FWD:
+      w.required = fwd_part_bytes(d, T, suffix_fwd_splits(d, n_mb, max_len));
+      w.total = std::max(w.required, fwd_part_bytes(d, T, suffix_fwd_pack_splits(d, n_mb, max_len)));
+      return w;
     case SPR_OP_SUFFIX_BWD: {
       w.dd_s = take(hq * T * 4);
       w.lse2_s = take(hq * T * 4);
@@ -389,9 +402,12 @@ WsLayout ws_layout(int op, const spr_dims* d, int32_t n_mb, int32_t max_len, int
         w.pdk = take(R * hkv * hd * eb);
         w.pdv = take(R * hkv * hd * eb);
       }
-      w.inner_bytes = ws_layout(bwd ? SPR_OP_SUFFIX_BWD : SPR_OP_SUFFIX_FWD, d, n_mb, max_len, (int32_t)R).total;
+      const WsLayout in = ws_layout(bwd ? SPR_OP_SUFFIX_BWD : SPR_OP_SUFFIX_FWD, d, n_mb, max_len, (int32_t)R);
+      w.inner_bytes = in.total;
+      w.required = off + in.required;
       w.inner = take(w.inner_bytes);
-      break;
+      w.total = off;
+      return w;
     }
     case SPR_OP_DENSE_BASELINE:
       w.dd_p = take(hq * P * 4);
@@ -413,14 +429,14 @@ WsLayout ws_layout(int op, const spr_dims* d, int32_t n_mb, int32_t max_len, int
     default:
       break;
   }
-  w.total = off;
+  w.total = w.required = off;
   return w;
 }
 
 spr_status check_ws(const WsLayout& w, const void* ws, size_t ws_bytes) {
-  if (w.total == 0) return SPR_OK;
+  if (w.required == 0) return SPR_OK;
   if (ws == nullptr) return fail(SPR_ERR_WORKSPACE, "workspace is null");
-  if (ws_bytes < w.total)
+  if (ws_bytes < w.required)
     return fail(SPR_ERR_WORKSPACE, "workspace too small: need " + std::to_string(w.total) +
                                        " bytes, got " + std::to_string(ws_bytes));
   if (((uintptr_t)ws & 15u) != 0) return fail(SPR_ERR_MISALIGNED, "workspace is not 16-byte aligned");
@@ -573,9 +589,15 @@ spr_status spr_suffix_attn_fwd(const spr_dims* dims, const void* k_p, const void
   a.seq_base = 0;
   a.n_seq = n_mb;
   a.n_split = suffix_fwd_splits(dims, n_mb, max_len);
+  const int pack = suffix_fwd_pack_splits(dims, n_mb, max_len);
+  if (pack > 0) {  // as many of its splits as the workspace holds (>= 2, or one)
+    a.n_split = pack;
+    const size_t have = ws != nullptr && ((uintptr_t)ws & 15u) == 0 ? ws_bytes : 0;
+    while (a.n_split > 1 && fwd_part_bytes(dims, T, a.n_split) > have) --a.n_split;
+  }
   if (a.n_split > 1) {
-    a.part_o = at<float>(ws, w.part_o);
-    a.part_lse = at<float>(ws, w.part_lse);
+    a.part_o = at<float>(ws, 0);
+    a.part_lse = at<float>(ws, fwd_part_o_bytes(dims, T, a.n_split));
   }
   if ((st = hip_check(launch_forward(dims, a, false, max_len, n_mb, stream), "suffix forward")) != SPR_OK)
     return st;
@@ -627,7 +649,7 @@ spr_status spr_suffix_attn_fwd_noalloc(const spr_dims* dims, const void* k_p, co
   spr_status st = check_dims(dims);
   if (st != SPR_OK) return st;
   if ((st = check_suffix_sizes(n_mb, max_len, total_len)) != SPR_OK) return st;
-  const size_t need = ws_layout(SPR_OP_SUFFIX_FWD, dims, n_mb, max_len, total_len).total;
+  const size_t need = ws_layout(SPR_OP_SUFFIX_FWD, dims, n_mb, max_len, total_len).required;
   if (need > kStaticScratchBytes)
     return fail(SPR_ERR_WORKSPACE, "these sizes need " + std::to_string(need) +
                                        " bytes of scratch; the static scratch holds " +
@@ -780,7 +802,7 @@ spr_status spr_suffix_attn_fwd_padded(const spr_dims* dims, const void* k_p, con
   const WsLayout w = ws_layout(SPR_OP_SUFFIX_FWD_PADDED, dims, n, s_max, 0);
   if ((st = check_ws(w, ws, ws_bytes)) != SPR_OK) return st;
   std::vector<Buf> all = bufs;
-  all.push_back({ws, w.total, "ws", false});
+  all.push_back({ws, std::min(w.total, ws_bytes), "ws", false});
   if ((st = check_aliasing({bufs[6], bufs[7], all.back()}, all)) != SPR_OK) return st;
   int32_t* cu = at<int32_t>(ws, w.cu);
   int32_t* lens_c = at<int32_t>(ws, w.lens_c);
@@ -794,7 +816,7 @@ spr_status spr_suffix_attn_fwd_padded(const spr_dims* dims, const void* k_p, con
   const RowMove in[] = {{q_s, pq, hq * hd * eb}, {k_s, pk, hkv * hd * eb}, {v_s, pv, hkv * hd * eb}};
   if ((st = hip_check(launch_rows_move(true, in, 3, seq_lens, cu, lens_c, n, s_max, stream), "gather")) != SPR_OK) return st;
   if ((st = spr_suffix_attn_fwd(dims, k_p, v_p, pq, pk, pv, cu, n, s_max, (int32_t)R, po, plse,
-                                at<char>(ws, w.inner), w.inner_bytes, stream)) != SPR_OK)
+                                at<char>(ws, w.inner), std::min(w.inner_bytes, ws_bytes - w.inner), stream)) != SPR_OK)
     return st;
   const RowMove out[] = {{po, o_s, hq * hd * eb}, {plse, lse_s, hq * 4}};
   if ((st = hip_check(launch_rows_move(false, out, 2, seq_lens, cu, lens_c, n, s_max, stream), "scatter")) != SPR_OK)

@@ -59,3 +59,45 @@ def test_packed_rows_match_oracle(gpu, shape):
         # element by element too: a row of another suffix or head is far off
         assert np.max(np.abs(outs["packed"][k] - want) / (1 + np.abs(want))) <= 2e-2, k
         assert np.array_equal(outs["packed"][k], outs["padded"][k]), k
+
+
+def _one_head_bytes(shape):
+    """workspace of the one-head form: its key splits' fp32 partials"""
+    n, ml, T = shape.n, max(shape.suffix_lens), shape.total_suffix
+    nrb = -(-ml // 128) * shape.num_q_heads * n
+    ns = max(1, min(-(-512 // nrb), max(1, shape.prefix_len // 256), 16))
+    up = lambda x: -(-x // 256) * 256
+    return 0 if ns == 1 else up(ns * T * shape.num_q_heads * shape.head_dim * 4) + up(ns * T * shape.num_q_heads * 4)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [CASES[0], CASES[1], GroupShape(32, 8, 64, 900, (20,) * 16, "bf16")],
+                         ids=["split", "split_d64", "none_needed"])
+def test_packed_rows_take_a_smaller_workspace(gpu, shape):
+    """A workspace of the one-head form's size (sized for other lengths) still
+    serves, with fewer key splits; a byte less is refused as it was there."""
+    import torch
+    from paper_2606_01143_amd import binding as B
+    from paper_2606_01143_amd.group import DeviceGroup
+    sys.stderr.write(f"\n[gpu-case] packed-row forward, small workspace {shape}\n")
+    sys.stderr.flush()
+    inp = make_group(shape, seed=4)
+    grp = DeviceGroup(inp, dense=False)
+    n, ml, T = shape.n, max(shape.suffix_lens), shape.total_suffix
+    need = _one_head_bytes(shape)
+    assert need < B.workspace_size(B.OP_SUFFIX_FWD, grp.dims, n, ml, T)
+    o, lse = torch.full_like(grp.out["o_s"], float("nan")), torch.full_like(grp.out["lse_s"], float("nan"))
+
+    def call(nbytes):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda") if nbytes else None
+        B.suffix_attn_fwd(grp.dims, grp.k_p, grp.v_p, grp.q_s, grp.k_s, grp.v_s, grp._mb_cu(0, n), n, ml, T, o, lse, ws)
+
+    if need:
+        with pytest.raises(B.SprError, match="SPR_ERR_WORKSPACE"):
+            call(need - 1)
+    ref = three_phase_reference(inp)
+    for nbytes in (need, need + need // 3 + 4096):
+        call(nbytes)
+        torch.cuda.synchronize()
+        assert max_abs_rel(o.float().cpu().numpy().astype(np.float64), ref["o_s"]) <= 2e-2
+        assert max_abs_rel(lse.cpu().numpy().astype(np.float64), ref["lse_s"].T) <= 2e-2
