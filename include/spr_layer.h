@@ -45,6 +45,11 @@ spr_status spr_swiglu_fwd(int64_t n, const void* g, const void* u, void* m, hipS
 spr_status spr_swiglu_bwd(int64_t n, const void* g, const void* u, const void* dm, void* dg, void* du,
                           hipStream_t stream);
 
+/* Weight-gradient sums (App. A.6: the prefix part plus every suffix part):
+ * dst = src (overwrite != 0) or dst += src, src [n] bf16, dst [n] fp32, n a
+ * multiple of 8. */
+spr_status spr_grad_accumulate(int64_t n, const void* src, float* dst, int32_t overwrite, hipStream_t stream);
+
 #ifdef __cplusplus
 }
 #endif

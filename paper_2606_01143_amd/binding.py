@@ -62,6 +62,7 @@ _SIGNATURES = {
     "spr_rope_bwd": ([c_int32, c_int32, c_int32, c_int32, c_double, _P, _P, _P], c_int32),
     "spr_swiglu_fwd": ([c_int64, _P, _P, _P, _P], c_int32),
     "spr_swiglu_bwd": ([c_int64, _P, _P, _P, _P, _P, _P], c_int32),
+    "spr_grad_accumulate": ([c_int64, _P, _P, c_int32, _P], c_int32),
     "spr_moe_stats_bytes": ([c_int32, POINTER(c_size_t)], c_int32),
     "spr_moe_stats_zero": ([c_int32, _P, _P], c_int32),
     "spr_moe_aux_workspace_size": ([c_int32, c_int32, POINTER(c_size_t)], c_int32),
@@ -415,6 +416,13 @@ def swiglu_bwd(g, u, dm, dg, du, stream=None):
     _need_all(n, 2, g=g, u=u, dm=dm, dg=dg, du=du)
     _check(lib().spr_swiglu_bwd(n, _ptr(g), _ptr(u), _ptr(dm), _ptr(dg), _ptr(du),
                                 _stream(stream)))
+
+
+def grad_accumulate(dst, src, overwrite=False, stream=None):
+    n = int(dst.numel())
+    _need_all(n, 4, dst=dst)
+    _need_all(n, 2, src=src)
+    _check(lib().spr_grad_accumulate(n, _ptr(src), _ptr(dst), 1 if overwrite else 0, _stream(stream)))
 
 
 def moe_stats_bytes(n_experts: int) -> int:

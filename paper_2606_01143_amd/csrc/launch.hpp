@@ -122,6 +122,8 @@ hipError_t launch_swiglu_fwd(long n, const void* g, const void* u, void* m, hipS
 hipError_t launch_swiglu_bwd(long n, const void* g, const void* u, const void* dm, void* dg, void* du,
                              hipStream_t st);
 
+hipError_t launch_grad_accumulate(long n, const void* src, float* dst, bool overwrite, hipStream_t st);
+
 // MoE router aux-loss accounting (kernels_moe.hip).  Statistics layout:
 // int64 count[E], double mass[E], int64 total, int64 invalid.
 int moe_blocks(int n_tokens);

@@ -1266,6 +1266,17 @@ spr_status spr_swiglu_bwd(int64_t n, const void* g, const void* u, const void* d
   return ok();
 }
 
+spr_status spr_grad_accumulate(int64_t n, const void* src, float* dst, int32_t overwrite, hipStream_t stream) {
+  if (n < 0 || n % 8 != 0) return fail(SPR_ERR_INVALID_ARG, "n must be a non-negative multiple of 8");
+  std::vector<Buf> bufs = {{src, (size_t)n * 2, "src", true}, {dst, (size_t)n * 4, "dst", true}};
+  spr_status st;
+  if ((st = check_bufs(bufs)) != SPR_OK) return st;
+  if ((st = check_aliasing({bufs[1]}, bufs)) != SPR_OK) return st;
+  if ((st = hip_check(launch_grad_accumulate(n, src, dst, overwrite != 0, stream), "grad accumulate")) != SPR_OK)
+    return st;
+  return ok();
+}
+
 // ------------------------------------------------------ MoE aux accounting
 namespace {
 spr_status check_moe(int32_t E, int32_t k) {

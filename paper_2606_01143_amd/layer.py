@@ -104,16 +104,16 @@ class DecoderLayer:
         shp, w = self.shape, self.w
         T, hq, hkv, d = dy.shape[0], shp.num_q_heads, shp.num_kv_heads, shp.head_dim
         dm = dy @ w["wd"].t()
-        dw["wd"] += (c["m"].t() @ dy).float()
+        self._add_dw(dw, "wd", c["m"].t() @ dy)
         dg, du = torch.empty_like(c["g"]), torch.empty_like(c["u"])
         B.swiglu_bwd(c["g"], c["u"], dm, dg, du)
         dn2 = dg @ w["wg"].t() + du @ w["wu"].t()
-        dw["wg"] += (c["n2"].t() @ dg).float()
-        dw["wu"] += (c["n2"].t() @ du).float()
+        self._add_dw(dw, "wg", c["n2"].t() @ dg)
+        self._add_dw(dw, "wu", c["n2"].t() @ du)
         dh = torch.empty_like(dy)
         B.rmsnorm_bwd(c["h"], c["r2"], dn2, dh, add=dy)
         do = (dh @ w["wo"].t()).view(T, hq, d).contiguous()
-        dw["wo"] += (c["o"].view(T, -1).t() @ dh).float()
+        self._add_dw(dw, "wo", c["o"].view(T, -1).t() @ dh)
         dq_r = torch.empty_like(c["q"])
         dk_r, dv = torch.empty_like(c["k"]), torch.empty_like(c["v"])
         attend_bwd(c, do, dq_r, dk_r, dv)
@@ -122,15 +122,27 @@ class DecoderLayer:
         B.rope_bwd(dk_r, dk, pos0, shp.rope_theta)
         dq2, dk2, dv2 = dq.view(T, -1), dk.view(T, -1), dv.view(T, -1)
         dn1 = dq2 @ w["wq"].t() + dk2 @ w["wk"].t() + dv2 @ w["wv"].t()
-        dw["wq"] += (c["n1"].t() @ dq2).float()
-        dw["wk"] += (c["n1"].t() @ dk2).float()
-        dw["wv"] += (c["n1"].t() @ dv2).float()
+        self._add_dw(dw, "wq", c["n1"].t() @ dq2)
+        self._add_dw(dw, "wk", c["n1"].t() @ dk2)
+        self._add_dw(dw, "wv", c["n1"].t() @ dv2)
         dx = torch.empty_like(dy)
         B.rmsnorm_bwd(c["x"], c["r1"], dn1, dx, add=dh)
         return dx
 
     def _zero_dw(self):
-        return {k: torch.zeros(v.shape, dtype=torch.float32, device=self.dev) for k, v in self.w.items()}
+        """Empty fp32 weight-gradient sums: a key is allocated by its first part."""
+        return {k: None for k in self.w}
+
+    def _add_dw(self, dw, key, part):
+        first = dw[key] is None
+        if first:
+            dw[key] = torch.empty(part.shape, dtype=torch.float32, device=self.dev)
+        B.grad_accumulate(dw[key], part, overwrite=first)
+
+    def _dw_sums(self, dw):
+        """The sums, zero for a key no part was added to."""
+        return {k: torch.zeros(w.shape, dtype=torch.float32, device=self.dev) if dw[k] is None else dw[k]
+                for k, w in self.w.items()}
 
     def _cu_of(self, s: int) -> torch.Tensor:
         if s not in self._cu:
@@ -168,7 +180,7 @@ class DecoderLayer:
         def prefix_attn_bwd(c, do, dq, dk, dv):
             B.prefix_bwd(dims, c["q"], c["k"], c["v"], c["o"], c["lse"], do, self.gk, self.gv, dq, dk, dv, self.ws)
         dx_p = self._backward(cp, self.g_y, 0, prefix_attn_bwd, dw)
-        return {"y_p": cp["y"], "y_s": y_s, "dx_p": dx_p, "dx_s": dx_s, "dw": dw}
+        return {"y_p": cp["y"], "y_s": y_s, "dx_p": dx_p, "dx_s": dx_s, "dw": self._dw_sums(dw)}
 
     # --------------------------------------------------------------- dense
     def _dims_for(self, L: int):
@@ -210,4 +222,4 @@ class DecoderLayer:
             if y_p is None:
                 y_p = c["y"][:P]
             del c
-        return {"y_p": y_p, "y_s": y_s, "dx_p": dx_p.to(torch.bfloat16), "dx_s": dx_s, "dw": dw}
+        return {"y_p": y_p, "y_s": y_s, "dx_p": dx_p.to(torch.bfloat16), "dx_s": dx_s, "dw": self._dw_sums(dw)}

@@ -296,7 +296,7 @@ class DecoderStack:
             g = layer._backward(c, g, 0, prefix_attn_bwd, dws[l])
             self._saved[l] = None
         mark("C")
-        return {"y_p": y_p, "y_s": y_s, "dx_p": g, "dx_s": dx_s, "dw": dws}
+        return {"y_p": y_p, "y_s": y_s, "dx_p": g, "dx_s": dx_s, "dw": [l._dw_sums(d) for l, d in zip(self.layers, dws)]}
 
     # --------------------------------------------------------------- dense
     def run_dense(self) -> Dict:
@@ -336,4 +336,4 @@ class DecoderStack:
             y_s.append(x[P:])
             if y_p is None:
                 y_p = x[:P]
-        return {"y_p": y_p, "y_s": y_s, "dx_p": dx_p.to(torch.bfloat16), "dx_s": dx_s, "dw": dws}
+        return {"y_p": y_p, "y_s": y_s, "dx_p": dx_p.to(torch.bfloat16), "dx_s": dx_s, "dw": [l._dw_sums(d) for l, d in zip(self.layers, dws)]}
