@@ -98,6 +98,10 @@ struct AttnArgs {
   // is the prefix key, or P + the packed row of a suffix key; a combine
   // kernel then sums the shares in index order and applies the epilogue.
   int32_t kv_rsplit;
+  // nonzero: only the prefix key tiles are cut and come first; the suffix key
+  // tiles, shorter than a share, keep their sweeps whole, write their outputs
+  // directly and fill the launch's tail
+  int32_t kv_split_prefix_only;
   float* part_dk;
   float* part_dv;
   float* gk;             // [P, Hkv, d] fp32

@@ -124,9 +124,6 @@ __device__ __forceinline__ void bwd_kv_body(const AttnArgs& a, const int bid, Kv
   const int r = lane & 31, h = lane >> 5;
   FragOffsets<D> fo;
   fo.init(lane);
-  // block b -> kv head b % Hkv (one XCD per kv head), row share, key tile
-  const int R = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
-  const int hk = bid % a.hkv, rs = (bid / a.hkv) % R, x = bid / a.hkv / R;
   const int G = a.hq / a.hkv;
 
   // ---- which KB keys: a prefix tile, or a tile of suffix s.  Launches
@@ -134,7 +131,16 @@ __device__ __forceinline__ void bwd_kv_body(const AttnArgs& a, const int bid, Kv
   // the start of a suffix carry about as many rows as a prefix tile, and the
   // shorter ones should not start last.
   const int n_sfx = PC ? 0 : a.n_seq * a.n_suffix_k_tiles;
-  const bool sfx_first = !PC && !a.prefix_rows;
+  const bool sfx_first = !PC && !a.prefix_rows && !a.kv_split_prefix_only;
+  // block b -> kv head b % Hkv (one XCD per kv head), row share, key tile
+  int R = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
+  const int hk = bid % a.hkv;
+  int rs = (bid / a.hkv) % R, x = bid / a.hkv / R;
+  if (!PC && a.kv_split_prefix_only && x >= a.n_prefix_k_tiles) {
+    x = bid / a.hkv - (R - 1) * a.n_prefix_k_tiles;
+    rs = 0;
+    R = 1;
+  }
   bool kpre;
   int k0, kseg, kbase;
   if (PC || (sfx_first ? x >= n_sfx : x < a.n_prefix_k_tiles)) {
@@ -955,7 +961,7 @@ namespace {
 // the row shares' partial dK/dV summed in share order, with the epilogue
 hipError_t launch_kv_combine(const AttnArgs& a, int head_dim, hipStream_t st) {
   const int n_pre = a.n_prefix_k_tiles > 0 ? a.P : 0;
-  const int n_sfx = a.n_seq * a.n_suffix_k_tiles > 0 ? a.total_len : 0;
+  const int n_sfx = a.n_seq * a.n_suffix_k_tiles > 0 && !a.kv_split_prefix_only ? a.total_len : 0;
   const long kthreads = ((long)n_pre + n_sfx) * a.hkv * (head_dim / 4);
   const unsigned kb = (unsigned)((kthreads + 255) / 256);
   ProfileScope pk("bwd_kv_combine", st);
@@ -976,8 +982,8 @@ hipError_t launch_bwd_bf16_kv_wide(const AttnArgs& a, int head_dim, hipStream_t 
     return hipErrorInvalidValue;
   const int R = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
   if (R > 1 && (a.part_dk == nullptr || a.part_dv == nullptr)) return hipErrorInvalidValue;
-  const long n_kt = (long)a.n_prefix_k_tiles + (long)a.n_seq * a.n_suffix_k_tiles;
-  const long n_kv = n_kt * a.hkv * R;
+  const long n_sfx = (long)a.n_seq * a.n_suffix_k_tiles * (a.kv_split_prefix_only ? 1 : R);
+  const long n_kv = ((long)a.n_prefix_k_tiles * R + n_sfx) * a.hkv;
   if (n_kv == 0) return hipSuccess;
   {
     ProfileScope ps("bwd_bf16", st);
@@ -1003,6 +1009,7 @@ hipError_t launch_bwd_bf16_kv_wide(const AttnArgs& a, int head_dim, hipStream_t 
 hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, int n_qz, bool deterministic,
                            hipStream_t st) {
   if (a.n_split > 1 && (a.prefix_rows || a.part_dq == nullptr)) return hipErrorInvalidValue;
+  if (a.kv_split_prefix_only) return hipErrorInvalidValue;  // the key-outer-only launch's
   const int R = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
   if (R > 1 && (a.part_dk == nullptr || a.part_dv == nullptr)) return hipErrorInvalidValue;
   // the atomic-dQ launch has no query-outer role, and needs an accumulator

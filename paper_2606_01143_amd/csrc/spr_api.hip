@@ -267,6 +267,61 @@ int suffix_bwd_kv_splits(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   const long kv = pre + (long)n_mb * causal_steps(max_len, g);
   return bwd_kv_splits(d, kv, max_steps);
 }
+// How a suffix backward runs its key-outer role: in the key-outer-only launch
+// or shared with the query-outer role, and in how many row shares.
+struct SuffixBwdPlan {
+  bool wide;
+  int shares;
+  bool fills;  // the shares are the prefix tiles' only, to fill their rounds
+};
+SuffixBwdPlan suffix_bwd_base_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) {
+  return {suffix_kv_wide(d, n_mb, max_len), suffix_bwd_kv_splits(d, n_mb, max_len), false};
+}
+// Where only its rounds keep the key-outer-only launch away (the prefix
+// tiles, equally long, leave the last round of 256 mostly empty), two things
+// can fill them: cutting every prefix sweep into R shares, and the suffix
+// tiles, started last.  The launch's time is estimated in steps per CU: full
+// rounds of shares, then the rest of the shares beside the suffix tiles.  The
+// smallest R with the lowest estimate is taken if that stays within 17% of an
+// even spread of the work, the suffix tiles are hardly longer than a share
+// (they would end the launch alone) and a share keeps kWideShareSteps steps.
+//
+// Measured, packed policy, whole steps in ms, shared launch -> this (Hq 32):
+//   Hkv 8, P = 2048, N = 4 / 16 x 1024    1.17 -> 1.07 / 4.13 -> 3.33
+//   Hkv 8, P = 8192, N = 4 / 8 x 1024     5.04 -> 4.88 / 7.60 -> 7.30
+//   Hkv 4, P = 5000, N = 6 x 800          3.38 -> 3.05
+//   Hkv 4, P = 8192, 16 ragged            14.6 -> 13.9
+//   Hkv 4, P = 10000, N = 3 x 1500 (R 1)  7.32 -> 7.24
+// and outside the bound: P = 2048, N = 4 with R = 3 (1.8 times the even
+// spread) 1.16, R = 1 (2.3 times) 1.35; P = 7000, N = 2 x 2000 with R = 1
+// (1.5 times) 4.25 -> 4.42.
+constexpr long kWideShareSteps = 128, kWideTileCost = 8;  // steps; a tile's prologue and epilogue
+SuffixBwdPlan suffix_bwd_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) {
+  const SuffixBwdPlan base = suffix_bwd_base_plan(d, n_mb, max_len);
+  if (base.wide || d->prefix_len == 0 || n_mb < 1 || max_len < 1 ||
+      !kv_wide(d, suffix_wide_steps(d, n_mb, max_len)))
+    return base;
+  const long g = d->num_q_heads / d->num_kv_heads, hkv = d->num_kv_heads, slots = bwd_bf16_kv_wide_slots();
+  const long n_pre = (long)tiles(d->prefix_len, (int)wide_bk()) * hkv;
+  const long steps = g * (((long)n_mb * max_len + 31) / 32);  // of a prefix tile
+  const long sfx_blocks = (long)n_mb * tiles(max_len, (int)wide_bk()) * hkv;
+  const long sfx_steps = (long)n_mb * causal_steps(max_len, g, wide_bk()) * hkv;
+  const long sfx_max = g * ((max_len + 31) / 32);
+  const long even = (n_pre * steps + sfx_steps) / slots;
+  const long sfx_work = sfx_steps + sfx_blocks * kWideTileCost;
+  long best_r = 0, best = 0;
+  for (long r = 1; r <= 8 && steps / r >= kWideShareSteps && 10 * (steps / r) >= 9 * sfx_max; ++r) {
+    const long len = (steps + r - 1) / r + kWideTileCost, n = n_pre * r;
+    const long rest = ((n % slots) * len + sfx_work) / slots;
+    const long t = n / slots * len + (n % slots > 0 ? std::max(len, rest) : rest);
+    if (best_r == 0 || t < best) {
+      best_r = r;
+      best = t;
+    }
+  }
+  if (best_r == 0 || 100 * best > 117 * even) return base;
+  return {true, (int)best_r, true};
+}
 // Phase C: causal prefix rows; key tile 0 sweeps all P
 int prefix_bwd_kv_splits(const spr_dims* d) {
   const long g = d->num_q_heads / d->num_kv_heads;
@@ -332,11 +387,37 @@ struct WsLayout {
   size_t pdq = 0, pdk = 0, pdv = 0, inner = 0, inner_bytes = 0;
   size_t total = 0;
   // bytes a call insists on: less than total where the packed-row suffix
-  // forward would use more splits than its one-head form.  A workspace sized
-  // for other lengths (the longest suffix's, say) then still serves, with the
-  // splits that fit it.
+  // forward would use more splits than its one-head form, or the suffix
+  // backward row shares to fill its rounds.  A workspace sized for other
+  // lengths (the longest suffix's, say) then still serves, with the splits or
+  // the plan that fit it.
   size_t required = 0;
 };
+
+// the suffix backward's regions under a plan
+WsLayout suffix_bwd_layout(const spr_dims* d, int32_t n_mb, int32_t max_len, int32_t total_len,
+                           const SuffixBwdPlan& plan) {
+  WsLayout w;
+  const size_t hq = d->num_q_heads, hkv = d->num_kv_heads, hd = d->head_dim;
+  const size_t P = d->prefix_len, T = total_len > 0 ? total_len : 0;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = off;
+    off = align_up(off + bytes, 256);
+    return at;
+  };
+  w.dd_s = take(hq * T * 4);
+  w.lse2_s = take(hq * T * 4);
+  if (d->dtype == SPR_F32 || atomic_dq(d)) w.dq_acc_s = take(T * hq * hd * 4);
+  const size_t ns = suffix_bwd_splits(d, n_mb, max_len);
+  if (ns > 1) w.part_dq = take(ns * T * hq * hd * 4);
+  if (plan.shares > 1) {
+    w.part_dk = take(plan.shares * (P + T) * hkv * hd * 4);
+    w.part_dv = take(plan.shares * (P + T) * hkv * hd * 4);
+  }
+  w.total = w.required = off;
+  return w;
+}
 
 WsLayout ws_layout(int op, const spr_dims* d, int32_t n_mb, int32_t max_len, int32_t total_len) {
   WsLayout w;
@@ -359,19 +440,11 @@ WsLayout ws_layout(int op, const spr_dims* d, int32_t n_mb, int32_t max_len, int
       w.required = fwd_part_bytes(d, T, suffix_fwd_splits(d, n_mb, max_len));
       w.total = std::max(w.required, fwd_part_bytes(d, T, suffix_fwd_pack_splits(d, n_mb, max_len)));
       return w;
-    case SPR_OP_SUFFIX_BWD: {
-      w.dd_s = take(hq * T * 4);
-      w.lse2_s = take(hq * T * 4);
-      if (f32 || atomic_dq(d)) w.dq_acc_s = take(T * hq * hd * 4);
-      const size_t ns = suffix_bwd_splits(d, n_mb, max_len);
-      if (ns > 1) w.part_dq = take(ns * T * hq * hd * 4);
-      const size_t rs = suffix_bwd_kv_splits(d, n_mb, max_len);
-      if (rs > 1) {
-        w.part_dk = take(rs * (P + T) * hkv * hd * 4);
-        w.part_dv = take(rs * (P + T) * hkv * hd * 4);
-      }
-      break;
-    }
+    case SPR_OP_SUFFIX_BWD:
+      w = suffix_bwd_layout(d, n_mb, max_len, total_len, suffix_bwd_plan(d, n_mb, max_len));
+      w.required = suffix_bwd_layout(d, n_mb, max_len, total_len, suffix_bwd_base_plan(d, n_mb, max_len)).total;
+      w.total = std::max(w.total, w.required);
+      return w;
     case SPR_OP_PREFIX_BWD: {
       w.dd_p = take(hq * P * 4);
       w.lse2_p = take(hq * P * 4);
@@ -437,7 +510,7 @@ spr_status check_ws(const WsLayout& w, const void* ws, size_t ws_bytes) {
   if (w.required == 0) return SPR_OK;
   if (ws == nullptr) return fail(SPR_ERR_WORKSPACE, "workspace is null");
   if (ws_bytes < w.required)
-    return fail(SPR_ERR_WORKSPACE, "workspace too small: need " + std::to_string(w.total) +
+    return fail(SPR_ERR_WORKSPACE, "workspace too small: need " + std::to_string(w.required) +
                                        " bytes, got " + std::to_string(ws_bytes));
   if (((uintptr_t)ws & 15u) != 0) return fail(SPR_ERR_MISALIGNED, "workspace is not 16-byte aligned");
   return SPR_OK;
@@ -710,8 +783,13 @@ spr_status spr_suffix_attn_bwd_accum(const spr_dims* dims, const void* k_p, cons
                            {gk_cache, P * hkv * hd * 4, "gk_cache", true},
                            {gv_cache, P * hkv * hd * 4, "gv_cache", true}};
   if ((st = check_bufs(bufs)) != SPR_OK) return st;
-  const WsLayout w = ws_layout(SPR_OP_SUFFIX_BWD, dims, n_mb, max_len, total_len);
-  if ((st = check_ws(w, ws, ws_bytes)) != SPR_OK) return st;
+  if ((st = check_ws(ws_layout(SPR_OP_SUFFIX_BWD, dims, n_mb, max_len, total_len), ws, ws_bytes)) != SPR_OK) return st;
+  SuffixBwdPlan plan = suffix_bwd_plan(dims, n_mb, max_len);
+  WsLayout w = suffix_bwd_layout(dims, n_mb, max_len, total_len, plan);
+  if (w.total > ws_bytes) {  // the plan that needs no more than the call insists on
+    plan = suffix_bwd_base_plan(dims, n_mb, max_len);
+    w = suffix_bwd_layout(dims, n_mb, max_len, total_len, plan);
+  }
   std::vector<Buf> all = bufs;
   all.push_back({ws, w.total, "ws", false});
   if ((st = check_aliasing({bufs[12], bufs[13]}, all)) != SPR_OK) return st;
@@ -749,12 +827,12 @@ spr_status spr_suffix_attn_bwd_accum(const spr_dims* dims, const void* k_p, cons
     a.n_split = suffix_bwd_splits(dims, n_mb, max_len);
     if (a.n_split > 1) a.part_dq = at<float>(ws, w.part_dq);
   }
-  a.kv_rsplit = suffix_bwd_kv_splits(dims, n_mb, max_len);
+  a.kv_rsplit = plan.shares;
   if (a.kv_rsplit > 1) {
     a.part_dk = at<float>(ws, w.part_dk);
     a.part_dv = at<float>(ws, w.part_dv);
   }
-  if (suffix_kv_wide(dims, n_mb, max_len)) {
+  if (plan.wide) {
     // the key-outer role alone on 192-key tiles, then the query-outer role
     // (as Phase C of a long prefix)
     AttnArgs kv = a;
@@ -763,6 +841,7 @@ spr_status spr_suffix_attn_bwd_accum(const spr_dims* dims, const void* k_p, cons
     kv.n_suffix_q_tiles = 0;
     kv.n_split = 1;
     kv.part_dq = nullptr;
+    kv.kv_split_prefix_only = plan.fills ? 1 : 0;
     if ((st = hip_check(launch_bwd_bf16_kv_wide(kv, dims->head_dim, stream), "suffix backward, dK/dV")) != SPR_OK)
       return st;
     AttnArgs q = a;
@@ -854,7 +933,7 @@ spr_status spr_suffix_attn_bwd_accum_padded(const spr_dims* dims, const void* k_
   const WsLayout w = ws_layout(SPR_OP_SUFFIX_BWD_PADDED, dims, n, s_max, 0);
   if ((st = check_ws(w, ws, ws_bytes)) != SPR_OK) return st;
   std::vector<Buf> all = bufs;
-  all.push_back({ws, w.total, "ws", false});
+  all.push_back({ws, std::min(w.total, ws_bytes), "ws", false});
   if ((st = check_aliasing({bufs[12], bufs[13], all.back()}, all)) != SPR_OK) return st;
   int32_t* cu = at<int32_t>(ws, w.cu);
   int32_t* lens_c = at<int32_t>(ws, w.lens_c);
@@ -870,7 +949,8 @@ spr_status spr_suffix_attn_bwd_accum_padded(const spr_dims* dims, const void* k_
                         {o_s, po, hq * hd * eb},  {lse_s, plse, hq * 4},      {do_s, pdo, hq * hd * eb}};
   if ((st = hip_check(launch_rows_move(true, in, 6, seq_lens, cu, lens_c, n, s_max, stream), "gather")) != SPR_OK) return st;
   if ((st = spr_suffix_attn_bwd_accum(dims, k_p, v_p, pq, pk, pv, po, plse, pdo, cu, n, s_max, (int32_t)R, pdq,
-                                      pdk, pdv, gk_cache, gv_cache, at<char>(ws, w.inner), w.inner_bytes,
+                                      pdk, pdv, gk_cache, gv_cache, at<char>(ws, w.inner),
+                                      std::min(w.inner_bytes, ws_bytes - w.inner),
                                       stream)) != SPR_OK)
     return st;
   const RowMove out[] = {{pdq, dq_s, hq * hd * eb}, {pdk, dk_s, hkv * hd * eb}, {pdv, dv_s, hkv * hd * eb}};

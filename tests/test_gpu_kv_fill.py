@@ -1,0 +1,79 @@
+"""Row shares that fill the rounds of the suffix backward's key-outer-only
+launch: prefix key tiles cut into R shares come first, the suffix key tiles,
+whole, last.  The choice is pinned on the CPU through the workspace sizes (R
+partials of dK and dV for R > 1), then whole packed schedules with R = 1 (order
+only), 2 and 4 are checked on sampled rows and keys, bitwise rerun, against the
+padded layout, and with a workspace that only holds the shared launch."""
+import numpy as np
+import pytest
+
+from sampled_checks import sampled_errors
+from synthetic import GroupShape, make_group
+from test_row_share_rule import _suffix_ws
+
+TOL = 2e-2
+CASES = [  # shape, shares of the prefix key tiles
+    (GroupShape(32, 4, 128, 5200, (760, 333, 800, 601, 640, 700), "bf16"), 2),
+    (GroupShape(32, 4, 64, 3000, (900, 899, 641, 900, 577, 800, 900, 640, 750), "bf16"), 4),
+    (GroupShape(32, 4, 128, 10000, (1500, 1311, 1402), "bf16"), 1),
+]
+IDS = ["r2_d128", "r4_d64", "r1_d128"]
+
+
+def _sizes(shape):
+    from paper_2606_01143_amd import binding as B
+    dims = B.make_dims(shape.num_q_heads, shape.num_kv_heads, shape.head_dim, shape.prefix_len, "bf16")
+    n, ml, T = shape.n, max(shape.suffix_lens), shape.total_suffix
+    return B, dims, n, ml, T
+
+
+def _fixed_bytes(shape):
+    """row statistic and log2 LSE, and the query-outer key splits' dQ"""
+    n, ml, T, hq = shape.n, max(shape.suffix_lens), shape.total_suffix, shape.num_q_heads
+    up = lambda x: -(-x // 256) * 256
+    nrb, nkt = -(-ml // 128) * hq * n, -(-shape.prefix_len // 64) + -(-ml // 64)
+    ns = 1 if nrb >= 512 else max(1, min(nkt // 16, -(-512 // nrb), 8))
+    return 2 * up(hq * T * 4) + (up(ns * T * hq * shape.head_dim * 4) if ns > 1 else 0)
+
+
+@pytest.mark.parametrize("shape,r", CASES, ids=IDS)
+def test_rule(shape, r):
+    B, dims, n, ml, T = _sizes(shape)
+    part = (shape.prefix_len + T) * shape.num_kv_heads * shape.head_dim * 4
+    want = _fixed_bytes(shape) + (2 * -(-r * part // 256) * 256 if r > 1 else 0)
+    assert B.workspace_size(B.OP_SUFFIX_BWD, dims, n, ml, T) == want
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,r", CASES, ids=IDS)
+def test_filled_rounds_match_oracle(gpu, shape, r):
+    import torch
+    from paper_2606_01143_amd.group import DeviceGroup
+    print(f"\n[gpu kv fill] {shape} shares={r}", flush=True)
+    inp = make_group(shape, seed=6)
+    mbs = [(0, shape.n)]
+    grp = DeviceGroup(inp, dense=False)
+    grp.run_schedule(mbs)
+    got = grp.fetch("schedule")
+    errs = sampled_errors(inp, got, np.random.default_rng(0))
+    assert all(v <= TOL for v in errs.values()), errs
+    grp.run_schedule(mbs)
+    again = grp.fetch("schedule")
+    assert all(np.array_equal(got[k], again[k]) for k in got)
+    if r > 1:
+        # the shared launch, in a workspace that holds no more than it needs
+        B, dims, n, ml, T = _sizes(shape)
+        base = _suffix_ws(shape.num_q_heads, shape.num_kv_heads, shape.head_dim, shape.prefix_len, n, ml, T, False)[0]
+        need = max(base, B.workspace_size(B.OP_PREFIX_BWD, dims),
+                   B.workspace_size(B.OP_SUFFIX_FWD, dims, n, ml, T))
+        if need < B.workspace_size(B.OP_SUFFIX_BWD, dims, n, ml, T):
+            grp.ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+            grp.run_schedule(mbs)
+            small = sampled_errors(inp, grp.fetch("schedule"), np.random.default_rng(0))
+            assert all(v <= TOL for v in small.values()), small
+    del grp
+    pad = DeviceGroup(inp, dense=False, layout="padded")
+    pad.run_schedule(mbs)
+    pad.gather_padded_outputs()
+    padded = pad.fetch("schedule")
+    assert all(np.array_equal(got[k], padded[k]) for k in got)
