@@ -295,9 +295,33 @@ SuffixBwdPlan suffix_bwd_base_plan(const spr_dims* d, int32_t n_mb, int32_t max_
 // and outside the bound: P = 2048, N = 4 with R = 3 (1.8 times the even
 // spread) 1.16, R = 1 (2.3 times) 1.35; P = 7000, N = 2 x 2000 with R = 1
 // (1.5 times) 4.25 -> 4.42.
+//
+// With less work than kKvWideMinSteps (one suffix per microbatch) the launch
+// still pays when its workgroups, prefix and suffix tiles together, fill one
+// round to 70% (the suffix forward running beside it uses the idle CUs) or
+// more rounds to 85%, uncut, and a prefix sweep has kWideLoneSteps steps, so
+// that its loop outweighs the tile's cache update.  Measured there, whole
+// steps in ms (Hq 32, d 128, one suffix per microbatch):
+//   Hkv 8, P = 4096, N = 8 x 512 (78% of a round)   2.54 -> 2.31
+//   Hkv 8, P = 5000, N = 8 x 512 (94%)              2.97 -> 2.76
+//   Hkv 8, P = 3700, N = 4 x 512 (72%)              1.48 -> 1.39
+//   Hkv 4, P = 10500, N = 4 x 700 (92%)             7.00 -> 6.70
+//   Hkv 8, P = 10240, N = 4 x 512 (89% of two)      5.43 -> 5.25
+// and outside: P = 3300 (66%) 1.24 -> 1.29, P = 8192 x 600 (73% of two)
+// 4.15 -> 4.24, P = 4400 x 300 (38 steps) 1.52 -> 1.56, d = 64 even.
 constexpr long kWideShareSteps = 128, kWideTileCost = 8;  // steps; a tile's prologue and epilogue
+constexpr long kWideLoneSteps = 48;
+bool suffix_kv_wide_lone(const spr_dims* d, int32_t n_mb, int32_t max_len) {
+  if (d->dtype != SPR_BF16 || atomic_dq(d) || d->head_dim != 128 || d->prefix_len == 0 || n_mb != 1 || max_len < 1)
+    return false;
+  const long g = d->num_q_heads / d->num_kv_heads, slots = bwd_bf16_kv_wide_slots();
+  const long blocks = (tiles(d->prefix_len, (int)wide_bk()) + tiles(max_len, (int)wide_bk())) * (long)d->num_kv_heads;
+  const long rounds = (blocks + slots - 1) / slots;
+  return g * ((max_len + 31) / 32) >= kWideLoneSteps && blocks * 100 >= (rounds == 1 ? 70 : 85) * slots * rounds;
+}
 SuffixBwdPlan suffix_bwd_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   const SuffixBwdPlan base = suffix_bwd_base_plan(d, n_mb, max_len);
+  if (!base.wide && base.shares == 1 && suffix_kv_wide_lone(d, n_mb, max_len)) return {true, 1, true};
   if (base.wide || d->prefix_len == 0 || n_mb < 1 || max_len < 1 ||
       !kv_wide(d, suffix_wide_steps(d, n_mb, max_len)))
     return base;

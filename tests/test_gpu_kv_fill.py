@@ -77,3 +77,21 @@ def test_filled_rounds_match_oracle(gpu, shape, r):
     pad.gather_padded_outputs()
     padded = pad.fetch("schedule")
     assert all(np.array_equal(got[k], padded[k]) for k in got)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [GroupShape(32, 4, 128, 8737, (500, 333), "bf16"),
+                                   GroupShape(32, 8, 128, 3700, (385, 512), "bf16")], ids=["hkv4", "hkv8"])
+def test_one_suffix_that_fills_a_round_matches_oracle(gpu, shape):
+    """One suffix per microbatch, its prefix and suffix key tiles filling one
+    round of the key-outer-only launch to 70%, partial tiles at both ends."""
+    from paper_2606_01143_amd.group import DeviceGroup
+    print(f"\n[gpu kv fill] lone {shape}", flush=True)
+    for s in shape.suffix_lens:
+        blocks = (-(-shape.prefix_len // 192) + -(-s // 192)) * shape.num_kv_heads
+        assert 0.7 * 256 <= blocks <= 256 and shape.group * -(-s // 32) >= 48
+    inp = make_group(shape, seed=7)
+    grp = DeviceGroup(inp, dense=False)
+    grp.run_schedule()
+    errs = sampled_errors(inp, grp.fetch("schedule"), np.random.default_rng(0))
+    assert all(v <= TOL for v in errs.values()), errs
