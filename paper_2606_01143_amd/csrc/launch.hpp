@@ -90,6 +90,7 @@ hipError_t launch_row_dot(int dtype, const void* dO, const void* O, int rows, in
                           const int32_t* cu, int seq, int hq, int head_dim, float* dd,
                           const float* lse, float* lse2, hipStream_t st);
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t st);
+hipError_t launch_fill_zero2(float* p, float* q, size_t n, hipStream_t st);
 // out = acc * scale (+ add when add != nullptr), converted to `dtype`
 hipError_t launch_convert(int dtype, const float* acc, float scale, const float* add,
                           void* out, size_t n, hipStream_t st);

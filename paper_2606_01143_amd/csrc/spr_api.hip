@@ -1254,8 +1254,7 @@ spr_status spr_gkv_cache_zero(const spr_dims* dims, float* gk_cache, float* gv_c
   if ((st = check_bufs({{gk_cache, n * 4, "gk_cache", true}, {gv_cache, n * 4, "gv_cache", true}})) != SPR_OK)
     return st;
   if (n == 0) return ok();
-  if ((st = hip_check(launch_fill_zero(gk_cache, n, stream), "cache zero")) != SPR_OK) return st;
-  if ((st = hip_check(launch_fill_zero(gv_cache, n, stream), "cache zero")) != SPR_OK) return st;
+  if ((st = hip_check(launch_fill_zero2(gk_cache, gv_cache, n, stream), "cache zero")) != SPR_OK) return st;
   return ok();
 }
 
