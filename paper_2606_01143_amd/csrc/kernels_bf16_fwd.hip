@@ -55,7 +55,7 @@ __device__ __forceinline__ RowBlock decode_row_block(const AttnArgs& a, int ntx)
   RowBlock rb;
   rb.split = b % a.n_split;
   b /= a.n_split;
-  rb.tile = ntx - 1 - b % ntx;  // rows with the most keys first
+  rb.tile = causal_tile_order(b % ntx, ntx, a.hq * a.n_split, gridDim.x);
   rb.z = b / ntx;
   rb.hq = hk * G + gi;
   return rb;

@@ -129,7 +129,7 @@ struct F32Rows {
   int lp0, seg_len, row_base, hq, hk;
 };
 template <int KS>
-__device__ __forceinline__ bool decode_rows(const AttnArgs& a, int bid, F32Rows& t) {
+__device__ __forceinline__ bool decode_rows(const AttnArgs& a, int bid, int n_blocks, F32Rows& t) {
   const int G = a.hq / a.hkv, ntp = QForm<KS>::tiles(a.n_prefix_q_tiles);
   const int ntx = ntp + QForm<KS>::tiles(a.n_suffix_q_tiles);
   int b = bid;
@@ -137,7 +137,7 @@ __device__ __forceinline__ bool decode_rows(const AttnArgs& a, int bid, F32Rows&
   b /= a.hkv;
   t.hq = t.hk * G + b % G;
   b /= G;
-  const int tile = ntx - 1 - b % ntx;
+  const int tile = causal_tile_order(b % ntx, ntx, a.hq, n_blocks);
   if (tile < ntp) {
     t.prefix = true;
     t.lp0 = tile * QForm<KS>::BQ;
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) float Ks[2][kF32Tile * D];
   __shared__ __attribute__((aligned(1024))) float Vs[2][kF32Tile * D];
   F32Rows t;
-  if (!decode_rows<KS>(a, blockIdx.x, t)) return;
+  if (!decode_rows<KS>(a, blockIdx.x, gridDim.x, t)) return;
   const int lane = threadIdx.x & 63, w = wave_id(), n = lane & 15, g = lane >> 4;
   F32Offsets<D> fo;
   fo.init(lane);
@@ -512,7 +512,7 @@ __device__ __forceinline__ void bwd_q_f32(const AttnArgs& a, int bid, float (*Ks
                                           float (*Vs)[kF32Tile * D]) {
   constexpr int NJ = D / 16, NKB = QForm<KS>::NKB;
   F32Rows t;
-  if (!decode_rows<KS>(a, bid, t)) return;
+  if (!decode_rows<KS>(a, bid, 1 << 30, t)) return;  // (beside the key-outer blocks: longest first)
   const int lane = threadIdx.x & 63, w = wave_id(), n = lane & 15, g = lane >> 4;
   F32Offsets<D> fo;
   fo.init(lane);
