@@ -110,7 +110,9 @@ __device__ __forceinline__ int dst_off(int key, int col) {
 // rows only), known at compile time, so the per-tile bookkeeping drops the
 // suffix-row cases; in the key-outer-only launch the twelve waves' scalar
 // instructions compete for the CU's scalar unit.
-template <int D, bool AQ, int NP = 2, bool PC = false>
+// FILL: the prefix tiles' row shares come first and fill the launch's rounds,
+// the suffix tiles follow uncut (AttnArgs::kv_split_prefix_only).
+template <int D, bool AQ, int NP = 2, bool PC = false, bool FILL = false>
 __device__ __forceinline__ void bwd_kv_body(const AttnArgs& a, const int bid, KvLds<D, AQ, NP>& L) {
   static_assert(NP == 2 || !AQ, "the atomic-dQ variant runs two pairs");
   static_assert(!PC || (NP > 2 && !AQ), "the Phase C form is the key-outer-only launch's");
@@ -124,23 +126,21 @@ __device__ __forceinline__ void bwd_kv_body(const AttnArgs& a, const int bid, Kv
   const int r = lane & 31, h = lane >> 5;
   FragOffsets<D> fo;
   fo.init(lane);
+  // block b -> kv head b % Hkv (one XCD per kv head), row share, key tile
+  const int R0 = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
+  const int hk = bid % a.hkv, rs0 = (bid / a.hkv) % R0, x0 = bid / a.hkv / R0;
   const int G = a.hq / a.hkv;
+  // (uncut suffix tiles after the cut prefix tiles)
+  const bool uncut = FILL && x0 >= a.n_prefix_k_tiles;
+  const int R = uncut ? 1 : R0, rs = uncut ? 0 : rs0;
+  const int x = uncut ? bid / a.hkv - (R0 - 1) * a.n_prefix_k_tiles : x0;
 
   // ---- which KB keys: a prefix tile, or a tile of suffix s.  Launches
   // without prefix rows take the suffix key tiles first: the causal tiles at
   // the start of a suffix carry about as many rows as a prefix tile, and the
   // shorter ones should not start last.
   const int n_sfx = PC ? 0 : a.n_seq * a.n_suffix_k_tiles;
-  const bool sfx_first = !PC && !a.prefix_rows && !a.kv_split_prefix_only;
-  // block b -> kv head b % Hkv (one XCD per kv head), row share, key tile
-  int R = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
-  const int hk = bid % a.hkv;
-  int rs = (bid / a.hkv) % R, x = bid / a.hkv / R;
-  if (!PC && a.kv_split_prefix_only && x >= a.n_prefix_k_tiles) {
-    x = bid / a.hkv - (R - 1) * a.n_prefix_k_tiles;
-    rs = 0;
-    R = 1;
-  }
+  const bool sfx_first = !PC && !FILL && !a.prefix_rows;
   bool kpre;
   int k0, kseg, kbase;
   if (PC || (sfx_first ? x >= n_sfx : x < a.n_prefix_k_tiles)) {
@@ -871,11 +871,11 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_bf16_kernel(AttnArgs a, int n
 // second product), so a third wave per SIMD fills more of the matrix core's
 // idle cycles; the pairs also share each Q/dO tile load.  Twelve waves keep
 // the SIMDs even (waves w, w + 4, w + 8 share one).
-template <int D, bool PC>
+template <int D, bool PC, bool FILL>
 __global__ __launch_bounds__(kKvWidePairs * 128, 1) void bwd_kv_wide_kernel(AttnArgs a, int n_kv) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[sizeof(KvLds<D, false, kKvWidePairs>)];
   if ((int)blockIdx.x < n_kv)
-    bwd_kv_body<D, false, kKvWidePairs, PC>(a, blockIdx.x, *(KvLds<D, false, kKvWidePairs>*)lds);
+    bwd_kv_body<D, false, kKvWidePairs, PC, FILL>(a, blockIdx.x, *(KvLds<D, false, kKvWidePairs>*)lds);
 }
 
 // dQ of every (suffix row, q head) = scale * the sum of the n_split partials
@@ -978,7 +978,8 @@ int bwd_bf16_kv_wide_slots() { return 256; }  // one workgroup per CU
 
 hipError_t launch_bwd_bf16_kv_wide(const AttnArgs& a, int head_dim, hipStream_t st) {
   // key-outer blocks only, 32 * kKvWidePairs-key tiles, default (non-atomic) mode
-  if (a.dq_atomic || a.n_prefix_q_tiles || a.n_suffix_q_tiles || a.n_split > 1)
+  if (a.dq_atomic || a.n_prefix_q_tiles || a.n_suffix_q_tiles || a.n_split > 1 ||
+      (a.kv_split_prefix_only && (a.prefix_rows || a.n_prefix_k_tiles == 0)))
     return hipErrorInvalidValue;
   const int R = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
   if (R > 1 && (a.part_dk == nullptr || a.part_dv == nullptr)) return hipErrorInvalidValue;
@@ -990,16 +991,19 @@ hipError_t launch_bwd_bf16_kv_wide(const AttnArgs& a, int head_dim, hipStream_t 
     // Phase C: prefix key tiles and causal prefix rows only
     const bool pc = a.prefix_rows && !a.suffix_rows && a.n_seq * a.n_suffix_k_tiles == 0;
     const dim3 grid((unsigned)n_kv), block(kKvWidePairs * 128);
-    if (head_dim == 64) {
-      if (pc)
-        hipLaunchKernelGGL((bwd_kv_wide_kernel<64, true>), grid, block, 0, st, a, (int)n_kv);
-      else
-        hipLaunchKernelGGL((bwd_kv_wide_kernel<64, false>), grid, block, 0, st, a, (int)n_kv);
-    } else if (pc) {
-      hipLaunchKernelGGL((bwd_kv_wide_kernel<128, true>), grid, block, 0, st, a, (int)n_kv);
-    } else {
-      hipLaunchKernelGGL((bwd_kv_wide_kernel<128, false>), grid, block, 0, st, a, (int)n_kv);
-    }
+    const bool fill = a.kv_split_prefix_only != 0;
+    if (pc && head_dim == 64)
+      hipLaunchKernelGGL((bwd_kv_wide_kernel<64, true, false>), grid, block, 0, st, a, (int)n_kv);
+    else if (pc)
+      hipLaunchKernelGGL((bwd_kv_wide_kernel<128, true, false>), grid, block, 0, st, a, (int)n_kv);
+    else if (fill && head_dim == 64)
+      hipLaunchKernelGGL((bwd_kv_wide_kernel<64, false, true>), grid, block, 0, st, a, (int)n_kv);
+    else if (fill)
+      hipLaunchKernelGGL((bwd_kv_wide_kernel<128, false, true>), grid, block, 0, st, a, (int)n_kv);
+    else if (head_dim == 64)
+      hipLaunchKernelGGL((bwd_kv_wide_kernel<64, false, false>), grid, block, 0, st, a, (int)n_kv);
+    else
+      hipLaunchKernelGGL((bwd_kv_wide_kernel<128, false, false>), grid, block, 0, st, a, (int)n_kv);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
