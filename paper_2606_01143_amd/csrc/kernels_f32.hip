@@ -419,9 +419,6 @@ __device__ __forceinline__ void bwd_kv_f32(const AttnArgs& a, int bid, F32KvLds<
     if (w == 1) rl.load(L.e[b], pick(rt.prefix, e_p, e_s) + hh, rt.row0, rt.nr, a.hq);
   };
 
-  // key tile 0's sweep is the launch's longest chain: its waves go before
-  // the query-outer waves that share their SIMDs
-  __builtin_amdgcn_s_setprio(1);
   int lj = t_lo / G, lg = t_lo % G, cj = lj, cg = lg;  // next tile to load, next to compute
   auto next = [&](int& j, int& gi) {
     if (++gi == G) {
