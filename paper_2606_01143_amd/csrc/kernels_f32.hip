@@ -670,6 +670,7 @@ hipError_t launch_bwd_f32(const AttnArgs& a, int head_dim, int n_qz, hipStream_t
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || R == 1 || n_kv == 0) return e;
   const size_t n4 = (size_t)a.P * a.hkv * head_dim / 4;
+  ProfileScope pk("bwd_kv_combine", st);
   hipLaunchKernelGGL(kv_combine_f32_kernel, dim3((unsigned)((n4 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
                      a, n4);
   return hipGetLastError();
