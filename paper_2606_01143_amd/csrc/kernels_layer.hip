@@ -282,7 +282,7 @@ hipError_t launch_rope(int tokens, int heads, int d, int pos0, double theta, con
   ProfileScope ps(inverse ? "rope_bwd" : "rope_fwd", st);
   const float sign = inverse ? -1.f : 1.f;
   if (d % 16 == 0 && d / 2 <= kRopeMaxHalf)
-    hipLaunchKernelGGL(rope_shared_kernel, dim3((tokens + kRopeTokens - 1) / kRopeTokens), dim3(kRowThreads), 0, st,
+    hipLaunchKernelGGL(rope_shared_kernel, dim3((tokens - 1) / kRopeTokens + 1), dim3(kRowThreads), 0, st,
                        (const bf16*)x, (bf16*)y, (long)tokens, heads, d, pos0, theta, sign);
   else
     hipLaunchKernelGGL(rope_kernel, dim3(tokens), dim3(kRowThreads), 0, st, (const bf16*)x, (bf16*)y, heads, d, pos0,
