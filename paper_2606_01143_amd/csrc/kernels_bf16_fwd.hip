@@ -82,7 +82,7 @@ __device__ __forceinline__ RowBlock decode_row_block(const AttnArgs& a, int ntx)
 // wherever it lies.
 // Measured at Hq 32, Hkv 8, d 128, P = 8191 with suffixes of 1, 24, 7 and 16
 // tokens: 69 us per call in one-head tiles, 32 us with packed rows per suffix,
-// 25 us with the shared prefix ranges.
+// 22.6 us with the shared prefix ranges.
 enum FwdForm { kFwdRows, kFwdWide, kFwdPack };
 template <int D, FwdForm FORM>
 __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D>::ELEMS],
@@ -496,10 +496,19 @@ int fwd_bf16_pack_split(int hq, int hkv, int n_mb, int max_len, int prefix_len) 
   // tiles give every CU two workgroups; else the prefix keys in as many
   // ranges of at least four 64-key tiles as make about two workgroups per
   // CU, plus one.  The partials then stay below 512 tiles of fp32 rows.
+  // Writing and merging a range's partials costs as much as sweeping about
+  // half a tile, so ranges of at most eight tiles (512 keys), 16 and more of
+  // them, are cut for 384 workgroups instead: two workgroups per CU -> this,
+  // Hq 32, Hkv 8, d 128, P = 8191, suffixes of 1, 24, 7, 16: 25.4 -> 22.6 us,
+  // four of 24: 32.4 -> 30.1; Hkv 4, d 64, P = 6000, suffixes of 8, 16, 24:
+  // 18.6 -> 16.6.  Beyond that line fewer ranges lose: at P = 16000, four of
+  // 24, ranges of 16 tiles 42.3 -> 44.0, and with six suffixes up to 60 (Hkv
+  // 4, P = 8000) four ranges instead of five 40.9 -> 47.6.
   const long tiles = fwd_bf16_pack_tiles(hq, hkv, max_len) * n_mb * hkv;
   if (tiles >= 512 || prefix_len < 4 * kTileRows) return 1;
   const long all = ((long)n_mb * max_len * (hq / hkv) + kFwdBQ - 1) / kFwdBQ * hkv;
-  const long ns = std::min(512 / all, (long)prefix_len / (4 * kTileRows));
+  const long fewer = std::max({384 / all, 16L, (long)prefix_len / (8 * kTileRows)});
+  const long ns = std::min({512 / all, fewer, (long)prefix_len / (4 * kTileRows)});
   return (int)std::max(1L, std::min(ns, 32L)) + 1;
 }
 

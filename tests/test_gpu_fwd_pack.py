@@ -37,6 +37,23 @@ def test_rule_picks_the_packed_form():
         assert not _packs(32, 8, s)
 
 
+@pytest.mark.parametrize("hq,hkv,d,P,n,ml,splits", [
+    (32, 8, 128, 8191, 4, 24, 17),    # 24 blocks a range: 16 ranges of eight tiles, not 21
+    (32, 8, 128, 16000, 4, 24, 22),   # ranges past eight tiles: two workgroups per CU
+    (32, 8, 128, 16000, 1, 60, 32),   # 16 blocks: 31 ranges of eight tiles, not 32
+    (32, 4, 64, 6000, 3, 24, 20),     # 20 blocks: 19
+    (32, 4, 128, 8000, 6, 60, 6),     # 92 blocks: fewer than 16 ranges keep two per CU
+    (32, 8, 128, 1024, 2, 4, 5),      # ranges of four tiles at least
+])
+def test_split_counts(hq, hkv, d, P, n, ml, splits):
+    """The reported workspace is the partials of the expected splits (outputs, then LSE,
+    each rounded up to 256 bytes)."""
+    from paper_2606_01143_amd import binding as B
+    up = lambda x: -(-x // 256) * 256
+    T = n * ml
+    got = B.workspace_size(B.OP_SUFFIX_FWD, B.make_dims(hq, hkv, d, P, "bf16"), n, ml, T)
+    assert got == up(splits * T * hq * d * 4) + up(splits * T * hq * 4)
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", CASES, ids=lambda s: f"hq{s.num_q_heads}_hkv{s.num_kv_heads}_d{s.head_dim}"
                                                        f"_p{s.prefix_len}_n{s.n}_max{max(s.suffix_lens)}")
