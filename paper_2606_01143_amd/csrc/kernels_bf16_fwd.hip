@@ -382,7 +382,10 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(AttnArgs a) {
     float mn = mx;
 #pragma unroll
     for (int i = 0; i < kB; ++i) {
-      if (j0 + i >= a.n_split) l[i] = -INFINITY;
+      if (j0 + i >= a.n_split) {  // past the last split: no weight, and no 0 * Inf either
+        l[i] = -INFINITY;
+        o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
       mn = fmaxf(mn, l[i]);
     }
     const float mu = mn == -INFINITY ? 0.f : mn;
