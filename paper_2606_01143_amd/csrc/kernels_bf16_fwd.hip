@@ -78,8 +78,9 @@ __device__ __forceinline__ RowBlock decode_row_block(const AttnArgs& a, int ntx)
 // by side, take n_split - 1 ranges of the prefix keys (every row sees all of
 // them, so the prefix is swept once for all suffixes), and blocks over one
 // suffix's rows take its own keys as the last split.  A row's result does
-// not depend on the suffixes beside it: its key tiles start at the same keys
-// wherever it lies.
+// not depend on the suffixes beside it (for the same number of suffixes and
+// longest one, which set the splits): its key tiles start at the same keys
+// wherever it lies, and its softmax reference moves by its own scores alone.
 // Measured at Hq 32, Hkv 8, d 128, P = 8191 with suffixes of 1, 24, 7 and 16
 // tokens: 69 us per call in one-head tiles, 32 us with packed rows per suffix,
 // 22.6 us with the shared prefix ranges.
@@ -244,9 +245,11 @@ __device__ __forceinline__ void fwd_body(const AttnArgs& a, bf16 (&Ks)[2][Tile<D
     // m is the reference the exponents are taken against, not necessarily
     // the running max: it moves (and O, l are rescaled) only when some row's
     // max exceeds it by more than kFwdSlack, so P = exp2(s - m) < 2^kFwdSlack.
-    // O / l and m + log2(l) do not depend on the reference.
+    // O / l and m + log2(l) do not depend on the reference, but P's rounding
+    // does: where a wave holds rows of several suffixes (PACK) each row moves
+    // by its own max only, so its bits do not follow its neighbours' scores.
     if (__builtin_expect(__any(mt > m + kFwdSlack), 0)) {
-      const float mn = fmaxf(m, mt);
+      const float mn = !PACK || mt > m + kFwdSlack ? fmaxf(m, mt) : m;
       const float corr = fast_exp2(m - (mn == -INFINITY ? 0.f : mn));
       l *= corr;
 #pragma unroll
