@@ -355,8 +355,8 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
     __syncthreads();
     if (ks == 1) return;
     const float m1 = xm[128 * r + lane], l1 = xm[128 * r + 64 + lane];
-    const float mn = fmaxf(m, m1);  // finite: every row sees a key of half 0
-    const float c0 = fast_exp2(m - mn), c1 = fast_exp2(m1 - mn);
+    const float mn = fmaxf(m, m1), mu = mn == -INFINITY ? 0.f : mn;  // (every visible score -Inf)
+    const float c0 = fast_exp2(m - mu), c1 = fast_exp2(m1 - mu);
     l = l * c0 + l1 * c1;
 #pragma unroll
     for (int db = 0; db < NJ; ++db) o[db] = o[db] * c0 + xo[(r * NJ + db) * 64 + lane] * c1;

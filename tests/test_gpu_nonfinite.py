@@ -125,3 +125,22 @@ def test_f32_infinite_value_at_the_last_key(gpu):
     got = grp.fetch("schedule")
     assert np.all(np.isposinf(got["o_s"][..., 3])) and np.all(np.isposinf(got["o_p"][P - 1, :, 3]))
     assert np.all(np.isfinite(got["o_p"][:P - 1])) and np.all(np.isfinite(np.delete(got["o_s"], 3, axis=-1)))
+
+
+@pytest.mark.parametrize("dtype,hq", [("f32", 4), ("f32", 64), ("bf16", 4)], ids=["f32_key_halves", "f32", "bf16"])
+def test_rows_whose_scores_are_all_minus_infinity(gpu, dtype, hq):
+    """log 0: LSE is -Inf for a row without any finite score, in every form."""
+    from paper_2606_01143_amd.group import DeviceGroup
+    shape = GroupShape(hq, 2, 64, 1030, (20, 37), dtype)
+    inp = make_group(shape, seed=3)
+    _say("all scores -Inf", shape)
+    for k in ("k_p", "k_s"):
+        inp[k][...] = -1.0
+    for k in ("q_p", "q_s"):
+        inp[k][:, 1] = 2.0 ** 127
+    grp = DeviceGroup(inp, dense=False)
+    grp.run_schedule()
+    got = grp.fetch("schedule")
+    for k in ("lse_p", "lse_s"):
+        assert np.all(np.isneginf(got[k][:, 1])), k
+        assert not np.any(np.isneginf(np.delete(got[k], 1, axis=1))), k
