@@ -313,7 +313,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
     mt = fmaxf(mt, __shfl_xor(mt, 32)) * a.scale_log2;
     if (__any(mt > m)) {
       const float mn = fmaxf(m, mt);
-      const float corr = fast_exp2(m - (mn == -INFINITY ? 0.f : mn));
+      const float corr = exp2f(m - (mn == -INFINITY ? 0.f : mn));
       l *= corr;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) o[j] *= corr;
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
     const float mu = m == -INFINITY ? 0.f : m;
 #pragma unroll
     for (int i = 0; i < 4 * NKB; ++i) {
-      const float p = fast_exp2(fmaf(st[i >> 2][i & 3], a.scale_log2, -mu));
+      const float p = exp2f(fmaf(st[i >> 2][i & 3], a.scale_log2, -mu));
       st[i >> 2][i & 3] = p;
       l += p;
     }
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
     if (ks == 1) return;
     const float m1 = xm[128 * r + lane], l1 = xm[128 * r + 64 + lane];
     const float mn = fmaxf(m, m1), mu = mn == -INFINITY ? 0.f : mn;  // (every visible score -Inf)
-    const float c0 = fast_exp2(m - mu), c1 = fast_exp2(m1 - mu);
+    const float c0 = exp2f(m - mu), c1 = exp2f(m1 - mu);
     l = l * c0 + l1 * c1;
 #pragma unroll
     for (int db = 0; db < NJ; ++db) o[db] = o[db] * c0 + xo[(r * NJ + db) * 64 + lane] * c1;
@@ -525,7 +525,7 @@ __device__ __forceinline__ void bwd_kv_f32(const AttnArgs& a, int bid, F32KvLds<
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const bool vis = 4 * g + e >= q_lo && 4 * g + e < q_hi;
-        const float p = fast_exp2(fmaf(s[e], a.scale_log2, -l4[e]));
+        const float p = exp2f(fmaf(s[e], a.scale_log2, -l4[e]));
         s[e] = vis ? p : 0.f;
         dp[e] = vis ? p * (dp[e] - e4[e]) : 0.f;
       }
@@ -630,7 +630,7 @@ __device__ __forceinline__ void bwd_q_f32(const AttnArgs& a, int bid, float (*Ks
       const bool extra = masked && !__all(times_zero(st[kb]) == 0.f);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float p = fast_exp2(fmaf(st[kb][e], a.scale_log2, -lse2));
+        const float p = exp2f(fmaf(st[kb][e], a.scale_log2, -lse2));
         ds[e] = 16 * kb + 4 * g + e < hi ? p * (pt[kb][e] - drow) : 0.f;
       }
       if (__builtin_expect(extra, 0)) add_visible<D>(dq, Kc, 16 * (ks + kb), ds, 0, hi - 16 * kb, n, g);
