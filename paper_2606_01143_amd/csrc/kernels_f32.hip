@@ -50,6 +50,10 @@ constexpr int kF32BK = 32;    // keys per key-outer workgroup
 __device__ __forceinline__ f32x4 mfma16(float a, float b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
+__device__ __forceinline__ float rounded_product(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
 __device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 
 // One wave's share (a quarter) of a 32-row tile's direct-to-LDS loads.
@@ -320,12 +324,18 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_f32_kernel(AttnArgs a) {
       m = mn;
     }
     const float mu = m == -INFINITY ? 0.f : m;
+    // The fused product differs from the rounded one in m by up to 2^-25 |m|.
+    // That cancels between O, l and the LSE as long as 2^(2^-25 |m|) is in
+    // range; beyond, the products are rounded alike.
+    if (__builtin_expect(__any(fabsf(mu) > 0x1p30f), 0)) {
 #pragma unroll
-    for (int i = 0; i < 4 * NKB; ++i) {
-      const float p = exp2f(fmaf(st[i >> 2][i & 3], a.scale_log2, -mu));
-      st[i >> 2][i & 3] = p;
-      l += p;
+      for (int i = 0; i < 4 * NKB; ++i) st[i >> 2][i & 3] = exp2f(rounded_product(st[i >> 2][i & 3], a.scale_log2) - mu);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4 * NKB; ++i) st[i >> 2][i & 3] = exp2f(fmaf(st[i >> 2][i & 3], a.scale_log2, -mu));
     }
+#pragma unroll
+    for (int i = 0; i < 4 * NKB; ++i) l += st[i >> 2][i & 3];
 #pragma unroll
     for (int b = 0; b < NKB; ++b) {
       const bool extra = masked && !rows_finite<D>(Vc, fo, 16 * (ks + b));
