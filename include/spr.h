@@ -51,8 +51,14 @@
  *          aligned (LSE and cu_seqlens: 4-byte aligned, so that microbatch
  *          slices of a packed group's LSE qualify).  The library never
  *          allocates, frees or keeps a pointer
- *          past the call.  Calls that take a workspace need at least the
- *          bytes spr_workspace_size reports (256-byte aligned).
+ *          past the call.  Calls that take a workspace need the bytes
+ *          spr_workspace_size reports (256-byte aligned).  The bf16 suffix
+ *          calls, packed and padded, also run in less where a form with
+ *          fewer partial sums exists (fewer key splits of the forward, fewer
+ *          or no row shares of the backward) and reject only what that form
+ *          cannot do with.  Their sums are then grouped differently: where
+ *          this header says that two calls agree bitwise, both have at least
+ *          the reported bytes.
  * Streams  Every call is asynchronous on `stream` and never synchronises the
  *          host.  The cache read-modify-write is not atomic across calls:
  *          every spr_suffix_attn_bwd_accum into one cache, and the
@@ -162,8 +168,8 @@ spr_status spr_suffix_attn_fwd(const spr_dims* dims, const void* k_p, const void
  * SPR_OP_SUFFIX_FWD) exceeds the scratch are rejected with
  * SPR_ERR_WORKSPACE and nothing is launched.  All calls on one GPU share
  * that GPU's scratch: two calls that overlap in time on one GPU (different
- * streams, or host threads) race and give undefined results; calls ordered
- * on one stream are safe.
+ * streams, or host threads) race and give undefined results, whatever their
+ * sizes; calls ordered on one stream are safe.
  */
 spr_status spr_suffix_attn_fwd_noalloc(const spr_dims* dims, const void* k_p, const void* v_p,
                                        const void* q_s, const void* k_s, const void* v_s,

@@ -148,11 +148,6 @@ int suffix_fwd_splits(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   return fwd_bf16_split(nrb, d->prefix_len);
 }
 
-// the packed-row form's, where the suffix forward takes that form; 0: it doesn't
-int suffix_fwd_pack_splits(const spr_dims* d, int32_t n_mb, int32_t max_len) {
-  if (d->dtype != SPR_BF16 || fwd_bf16_pack_tiles(d->num_q_heads, d->num_kv_heads, max_len) == 0) return 0;
-  return fwd_bf16_pack_split(d->num_q_heads, d->num_kv_heads, n_mb, max_len, d->prefix_len);
-}
 // bytes of the suffix forward's partials (outputs, then LSE) for ns splits of
 // T rows
 size_t fwd_part_o_bytes(const spr_dims* d, size_t T, size_t ns) {
@@ -160,6 +155,17 @@ size_t fwd_part_o_bytes(const spr_dims* d, size_t T, size_t ns) {
 }
 size_t fwd_part_bytes(const spr_dims* d, size_t T, size_t ns) {
   return ns <= 1 ? 0 : fwd_part_o_bytes(d, T, ns) + align_up(ns * T * d->num_q_heads * 4, 256);
+}
+// The packed-row form's key splits, where the suffix forward takes that form;
+// 0: it doesn't.  Their partials always fit the static scratch (beyond it the
+// rows alone fill the chip), so that the call without a workspace takes the
+// same splits; the one-head form's may not, and that call then refuses.
+constexpr size_t kStaticScratchBytes = size_t(64) << 20;
+int suffix_fwd_pack_splits(const spr_dims* d, int32_t n_mb, int32_t max_len) {
+  if (d->dtype != SPR_BF16 || fwd_bf16_pack_tiles(d->num_q_heads, d->num_kv_heads, max_len) == 0) return 0;
+  int ns = fwd_bf16_pack_split(d->num_q_heads, d->num_kv_heads, n_mb, max_len, d->prefix_len);
+  while (ns > 1 && fwd_part_bytes(d, (size_t)n_mb * max_len, ns) > kStaticScratchBytes) --ns;
+  return ns;
 }
 
 bool atomic_dq(const spr_dims* d);
@@ -709,7 +715,6 @@ spr_status spr_suffix_attn_fwd(const spr_dims* dims, const void* k_p, const void
 // not a device address: the address is looked up once per device with
 // hipGetSymbolAddress and only that pointer is passed to kernels.
 namespace {
-constexpr size_t kStaticScratchBytes = size_t(64) << 20;
 constexpr int kMaxDevices = 64;
 }  // namespace
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
