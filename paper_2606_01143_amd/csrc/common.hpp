@@ -110,6 +110,11 @@ struct AttnArgs {
   // tiles, shorter than a share, keep their sweeps whole, write their outputs
   // directly and fill the launch's tail
   int32_t kv_split_prefix_only;
+  // not null: key-outer blocks and the share combine run only if *gate ==
+  // gate_value (a choice between two launches that depends on the lengths on
+  // the device)
+  const int32_t* gate;
+  int32_t gate_value;
 };
 
 enum PkMode { kPkAccumulate = 0, kPkInject = 1 };

@@ -836,8 +836,9 @@ __device__ __forceinline__ void bwd_q_body(const AttnArgs& a, const int bid, bf1
 // of a microbatch share the GPU (a suffix microbatch alone fills neither).
 // The heavier role goes first; both segments start on a multiple of 8 blocks
 // so the XCD mapping of each role holds.  The atomic-dQ variant (AQ) has the
-// key-outer role only: its blocks also add dQ into fp32 accumulators.
-template <int D, bool AQ>
+// key-outer role only: its blocks also add dQ into fp32 accumulators.  GATED:
+// the key-outer blocks leave where the gate gave their work to another launch.
+template <int D, bool AQ, bool GATED = false>
 __global__ __launch_bounds__(kThreads, 2) void bwd_bf16_kernel(AttnArgs a, int n_first, int n_kv,
                                                                int n_q, int kv_first) {
   constexpr int TE = Tile<D>::ELEMS;
@@ -855,6 +856,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_bf16_kernel(AttnArgs a, int n
     const int bid = first ? b : b - n_first;
     // the first segment is padded to a multiple of 8 blocks: padding exits
     if (first == (kv_first != 0)) {
+      if (GATED && *a.gate != a.gate_value) return;
       if (bid < n_kv) bwd_kv_body<D, false>(a, bid, *(KvLds<D, false>*)lds);
     } else {
       bf16(*tiles)[TE] = (bf16(*)[TE])lds;
@@ -874,6 +876,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_bf16_kernel(AttnArgs a, int n
 template <int D, bool PC, bool FILL>
 __global__ __launch_bounds__(kKvWidePairs * 128, 1) void bwd_kv_wide_kernel(AttnArgs a, int n_kv) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[sizeof(KvLds<D, false, kKvWidePairs>)];
+  if (FILL && a.gate != nullptr && *a.gate != a.gate_value) return;
   if ((int)blockIdx.x < n_kv)
     bwd_kv_body<D, false, kKvWidePairs, PC, FILL>(a, blockIdx.x, *(KvLds<D, false, kKvWidePairs>*)lds);
 }
@@ -910,6 +913,7 @@ __global__ __launch_bounds__(256) void bwd_dq_combine_kernel(AttnArgs a) {
 template <int D>
 __global__ __launch_bounds__(256) void bwd_kv_combine_kernel(AttnArgs a, int n_pre, int n_sfx) {
   constexpr int TPR = D / 4;
+  if (a.gate != nullptr && *a.gate != a.gate_value) return;
   const long idx = (long)blockIdx.x * 256 + threadIdx.x;
   const long kh = idx / TPR;  // (key index) * hkv + kv head
   const int c = (int)(idx % TPR);
@@ -979,7 +983,8 @@ int bwd_bf16_kv_wide_slots() { return 256; }  // one workgroup per CU
 hipError_t launch_bwd_bf16_kv_wide(const AttnArgs& a, int head_dim, hipStream_t st) {
   // key-outer blocks only, 32 * kKvWidePairs-key tiles, default (non-atomic) mode
   if (a.dq_atomic || a.n_prefix_q_tiles || a.n_suffix_q_tiles || a.n_split > 1 ||
-      (a.kv_split_prefix_only && (a.prefix_rows || a.n_prefix_k_tiles == 0)))
+      (a.kv_split_prefix_only && (a.prefix_rows || a.n_prefix_k_tiles == 0)) ||
+      (a.gate != nullptr && !a.kv_split_prefix_only))
     return hipErrorInvalidValue;
   const int R = a.kv_rsplit > 1 ? a.kv_rsplit : 1;
   if (R > 1 && (a.part_dk == nullptr || a.part_dv == nullptr)) return hipErrorInvalidValue;
@@ -1020,6 +1025,7 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, int n_qz, bool deter
   // for every kind of row its key tiles sweep
   (void)deterministic;  // the default path has no atomics; the atomic one is asked for explicitly
   const bool aq = a.dq_atomic != 0;
+  if (aq && a.gate != nullptr) return hipErrorInvalidValue;
   if (aq && (a.n_prefix_q_tiles || a.n_suffix_q_tiles || a.n_split > 1 ||
              (a.prefix_rows && a.dq_acc_p == nullptr) || (a.n_seq > 0 && a.dq_acc_s == nullptr)))
     return hipErrorInvalidValue;
@@ -1059,12 +1065,15 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, int n_qz, bool deter
     else
       hipLaunchKernelGGL((bwd_bf16_kernel<128, true>), dim3((unsigned)nb), dim3(kThreads), 0, st, a,
                          (int)n_first, (int)n_kv, 0, 1);
-  } else if (head_dim == 64) {
-    hipLaunchKernelGGL((bwd_bf16_kernel<64, false>), dim3((unsigned)nb), dim3(kThreads), 0, st, a,
-                       (int)n_first, (int)n_kv, (int)n_q, kv_first);
   } else {
-    hipLaunchKernelGGL((bwd_bf16_kernel<128, false>), dim3((unsigned)nb), dim3(kThreads), 0, st, a,
-                       (int)n_first, (int)n_kv, (int)n_q, kv_first);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kThreads), 0, st, a, (int)n_first, (int)n_kv, (int)n_q,
+                         kv_first);
+    };
+    if (a.gate != nullptr)
+      head_dim == 64 ? launch(bwd_bf16_kernel<64, false, true>) : launch(bwd_bf16_kernel<128, false, true>);
+    else
+      head_dim == 64 ? launch(bwd_bf16_kernel<64, false>) : launch(bwd_bf16_kernel<128, false>);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1081,6 +1090,18 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, int n_qz, bool deter
 }
 
 int bwd_bf16_block_q() { return kQBQ; }
+
+namespace {
+__global__ void fill_gate_kernel(FillRule r, const int32_t* cu, int n, int32_t* gate) {
+  if (threadIdx.x == 0) *gate = fill_pays(r, cu[n]) ? 1 : 0;
+}
+}  // namespace
+
+hipError_t launch_fill_gate(const FillRule& r, const int32_t* cu, int n, int32_t* gate, hipStream_t st) {
+  ProfileScope ps("fill_gate", st);
+  hipLaunchKernelGGL(fill_gate_kernel, dim3(1), dim3(64), 0, st, r, cu, n, gate);
+  return hipGetLastError();
+}
 
 int bwd_bf16_kvsplit(long kv_tiles, long max_tiles, bool kv_alone, int slots) {
   // kv_tiles: the key-outer role's (32-row tile, q head) steps over all its

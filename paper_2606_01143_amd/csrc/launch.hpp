@@ -75,6 +75,43 @@ int bwd_bf16_kv_wide_slots();
 int bwd_bf16_qsplit(int n_row_blocks, int n_key_tiles);
 int bwd_bf16_kvsplit(long kv_tiles, long max_tiles, bool kv_alone, int slots = 512);
 int bwd_bf16_block_q();
+
+// The suffix backward's key-outer-only launch with filled rounds (the prefix
+// tiles' row shares first, whole suffix tiles after them), for sizes the host
+// knows; whether it pays depends on the microbatch's rows in all, which the
+// host knows of packed suffixes only.
+constexpr long kKvWideMinSteps = 32768;                    // see kv_wide
+constexpr long kWideShareSteps = 128, kWideTileCost = 8;  // steps; a tile's prologue and epilogue
+struct FillRule {
+  long prefix_tiles, group, hkv;  // prefix key tiles over all kv heads, q heads per kv head, kv heads
+  long n, max_len, causal;        // suffixes, the longest, its key tiles' steps of one kv head
+  long shares, slots;             // row shares of a prefix tile, workgroups resident at once
+};
+// The launch's time, in steps per CU: the rounds of shares; suffix tiles in
+// the slots the last round leaves and after it; never less than the longest
+// suffix tile begun after the full rounds, nor than the even spread plus
+// half of it.  It pays within 25% of the even spread, where the shares are
+// long enough and hardly shorter than that tile.  Integers only: host and
+// device agree.
+__host__ __device__ inline bool fill_pays(const FillRule& r, long rows) {
+  const long steps = r.group * ((rows + 31) / 32), whole = steps / r.shares;
+  const long share = (steps + r.shares - 1) / r.shares + kWideTileCost, tiles = r.prefix_tiles * r.shares;
+  const long longest = r.group * ((r.max_len + 31) / 32);
+  const long suffix = r.causal * (256 * rows / r.max_len) / 256 * r.hkv;
+  const long work = suffix + (rows / 192 + r.n) * r.hkv * kWideTileCost;
+  const long full = tiles / r.slots * share, last = tiles % r.slots;
+  const long rest = (last * share + work) / r.slots, after = full + longest + kWideTileCost;
+  const long spread = (tiles * share + work) / r.slots + (longest + kWideTileCost) / 2;
+  long t = full + (last > 0 && rest < share ? share : rest);
+  if (t < after) t = after;
+  if (t < spread) t = spread;
+  const long useful = r.prefix_tiles * steps + suffix;
+  return useful >= kKvWideMinSteps && whole >= kWideShareSteps && 10 * whole >= 9 * longest &&
+         100 * t * r.slots <= 125 * useful;
+}
+// *gate = fill_pays(r, cu[n]) as 0 or 1
+hipError_t launch_fill_gate(const FillRule& r, const int32_t* cu, int n, int32_t* gate, hipStream_t st);
+
 int f32_block_q();
 int f32_block_k();
 // row shares of Phase C's key-outer role in fp32 storage (1 + group / 2 at most)

@@ -225,7 +225,6 @@ bool fwd_wide(const spr_dims* d, long wide_tiles) {
 // same rule serves Phase C, the dense baseline's per-trajectory backward and
 // the suffix backward (the packed dense baseline's whole trajectories among
 // them).
-constexpr long kKvWideMinSteps = 32768;
 bool kv_wide(const spr_dims* d, long wide_steps) {
   return d->dtype == SPR_BF16 && !atomic_dq(d) && wide_steps * d->num_kv_heads >= kKvWideMinSteps;
 }
@@ -279,28 +278,35 @@ struct SuffixBwdPlan {
   bool wide;
   int shares;
   bool fills;  // the shares are the prefix tiles' only, to fill their rounds
+  bool by_rows;  // taken only if fill_pays for the microbatch's rows
 };
 SuffixBwdPlan suffix_bwd_base_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) {
-  return {suffix_kv_wide(d, n_mb, max_len), suffix_bwd_kv_splits(d, n_mb, max_len), false};
+  return {suffix_kv_wide(d, n_mb, max_len), suffix_bwd_kv_splits(d, n_mb, max_len), false, false};
 }
 // Where only its rounds keep the key-outer-only launch away (the prefix
 // tiles, equally long, leave the last round of 256 mostly empty), two things
 // can fill them: cutting every prefix sweep into R shares, and the suffix
-// tiles, started last.  The launch's time is estimated in steps per CU: full
-// rounds of shares, then the rest of the shares beside the suffix tiles.  The
-// smallest R with the lowest estimate is taken if that stays within 17% of an
-// even spread of the work, the suffix tiles are hardly longer than a share
-// (they would end the launch alone) and a share keeps kWideShareSteps steps.
+// tiles, started last.  R is chosen for suffixes of equal length, from n_mb
+// and max_len alone, so that packed and padded calls sum alike: the smallest
+// with the lowest estimate (full rounds of shares, then the rest of the
+// shares beside the suffix tiles) if that stays within 17% of an even spread
+// of the work, the suffix tiles are hardly longer than a share and a share
+// keeps kWideShareSteps steps.  Whether the form is then taken depends on the
+// rows there are (fill_pays): where the lengths differ, the shares are
+// shorter, and the longest suffix's tiles, uncut and last, would end the
+// launch alone.  Packed calls know the rows on the host; padded calls decide
+// on the device, between this launch and the shared one's key-outer blocks.
 //
-// Measured, packed policy, whole steps in ms, shared launch -> this (Hq 32):
-//   Hkv 8, P = 2048, N = 4 / 16 x 1024    1.17 -> 1.07 / 4.13 -> 3.33
-//   Hkv 8, P = 8192, N = 4 / 8 x 1024     5.04 -> 4.88 / 7.60 -> 7.30
-//   Hkv 4, P = 5000, N = 6 x 800          3.38 -> 3.05
-//   Hkv 4, P = 8192, 16 ragged            14.6 -> 13.9
-//   Hkv 4, P = 10000, N = 3 x 1500 (R 1)  7.32 -> 7.24
-// and outside the bound: P = 2048, N = 4 with R = 3 (1.8 times the even
-// spread) 1.16, R = 1 (2.3 times) 1.35; P = 7000, N = 2 x 2000 with R = 1
-// (1.5 times) 4.25 -> 4.42.
+// Suffix backward calls measured, shared launch / this, on 950 packed groups
+// (Hq 8-32, Hkv 4 and 8, d 64 and 128, P 500-20000, 2 to 16 suffixes of up to
+// 2048, equal, drawn, and one long among short): 486 have an R, and of the 373
+// unequal ones among them 184 would be slower, down to 0.43. fill_pays takes
+// 116, at 0.99 to 2.16, geometric mean 1.19, and none of the 184; the launch
+// keeps at least 70% of its slots busy there.  Examples in us:
+//   Hq 32, Hkv 8, d 64,  P = 1418, 16 x 1836               6000 -> 2776
+//   Hq 32, Hkv 8, d 128, P = 1590, 10 x 1834               4198 -> 2714
+//   Hq 32, Hkv 4, d 128, P = 508, 1315 among 10 short      not taken: 196, R = 8 460
+//   Hq 32, Hkv 8, d 128, P = 2775, 1728 among 8 short      not taken: 731, R = 2 846
 //
 // With less work than kKvWideMinSteps (one suffix per microbatch) the launch
 // still pays when its workgroups, prefix and suffix tiles together, fill one
@@ -315,7 +321,6 @@ SuffixBwdPlan suffix_bwd_base_plan(const spr_dims* d, int32_t n_mb, int32_t max_
 //   Hkv 8, P = 10240, N = 4 x 512 (89% of two)      5.43 -> 5.25
 // and outside: P = 3300 (66%) 1.24 -> 1.29, P = 8192 x 600 (73% of two)
 // 4.15 -> 4.24, P = 4400 x 300 (38 steps) 1.52 -> 1.56, d = 64 even.
-constexpr long kWideShareSteps = 128, kWideTileCost = 8;  // steps; a tile's prologue and epilogue
 constexpr long kWideLoneSteps = 48;
 bool suffix_kv_wide_lone(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   if (d->dtype != SPR_BF16 || atomic_dq(d) || d->head_dim != 128 || d->prefix_len == 0 || n_mb != 1 || max_len < 1)
@@ -327,7 +332,7 @@ bool suffix_kv_wide_lone(const spr_dims* d, int32_t n_mb, int32_t max_len) {
 }
 SuffixBwdPlan suffix_bwd_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   const SuffixBwdPlan base = suffix_bwd_base_plan(d, n_mb, max_len);
-  if (!base.wide && base.shares == 1 && suffix_kv_wide_lone(d, n_mb, max_len)) return {true, 1, true};
+  if (!base.wide && base.shares == 1 && suffix_kv_wide_lone(d, n_mb, max_len)) return {true, 1, true, false};
   if (base.wide || d->prefix_len == 0 || n_mb < 1 || max_len < 1 ||
       !kv_wide(d, suffix_wide_steps(d, n_mb, max_len)))
     return base;
@@ -350,7 +355,12 @@ SuffixBwdPlan suffix_bwd_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) 
     }
   }
   if (best_r == 0 || 100 * best > 117 * even) return base;
-  return {true, (int)best_r, true};
+  return {true, (int)best_r, true, true};
+}
+FillRule suffix_fill_rule(const spr_dims* d, int32_t n_mb, int32_t max_len, int shares) {
+  const long g = d->num_q_heads / d->num_kv_heads, hkv = d->num_kv_heads;
+  return {(long)tiles(d->prefix_len, (int)wide_bk()) * hkv, g, hkv, n_mb, max_len,
+          causal_steps(max_len, g, wide_bk()), shares, bwd_bf16_kv_wide_slots()};
 }
 // Phase C: causal prefix rows; key tile 0 sweeps all P
 int prefix_bwd_kv_splits(const spr_dims* d) {
@@ -415,6 +425,7 @@ struct WsLayout {
   // padded layout: offsets, clamped lengths, packed copies, inner workspace
   size_t cu = 0, lens_c = 0, pq = 0, pk = 0, pv = 0, po = 0, plse = 0, pdo = 0;
   size_t pdq = 0, pdk = 0, pdv = 0, inner = 0, inner_bytes = 0;
+  size_t gate = 0;  // after the inner workspace (total, not required)
   size_t total = 0;
   // bytes a call insists on: less than total where the packed-row suffix
   // forward would use more splits than its one-head form, or the suffix
@@ -509,6 +520,7 @@ WsLayout ws_layout(int op, const spr_dims* d, int32_t n_mb, int32_t max_len, int
       w.inner_bytes = in.total;
       w.required = off + in.required;
       w.inner = take(w.inner_bytes);
+      if (bwd && suffix_bwd_plan(d, n_mb, max_len).by_rows) w.gate = take(4);
       w.total = off;
       return w;
     }
@@ -785,13 +797,16 @@ spr_status spr_check_cu_seqlens(const int32_t* cu_host, int32_t n_mb, int32_t ma
   return ok();
 }
 
-spr_status spr_suffix_attn_bwd_accum(const spr_dims* dims, const void* k_p, const void* v_p,
-                                     const void* q_s, const void* k_s, const void* v_s,
-                                     const void* o_s, const float* lse_s, const void* do_s,
-                                     const int32_t* cu_seqlens, int32_t n_mb, int32_t max_len,
-                                     int32_t total_len, void* dq_s, void* dk_s, void* dv_s,
-                                     float* gk_cache, float* gv_cache, void* ws, size_t ws_bytes,
-                                     hipStream_t stream) {
+namespace {
+// `padded`: total_len bounds the rows, which only the device knows, and a
+// choice that depends on them goes through `gate` (null: no room for it)
+spr_status suffix_bwd_accum(const spr_dims* dims, const void* k_p, const void* v_p,
+                            const void* q_s, const void* k_s, const void* v_s,
+                            const void* o_s, const float* lse_s, const void* do_s,
+                            const int32_t* cu_seqlens, int32_t n_mb, int32_t max_len,
+                            int32_t total_len, void* dq_s, void* dk_s, void* dv_s,
+                            float* gk_cache, float* gv_cache, void* ws, size_t ws_bytes,
+                            hipStream_t stream, bool padded, int32_t* gate) {
   spr_status st = check_dims(dims);
   if (st != SPR_OK) return st;
   if ((st = check_suffix_sizes(n_mb, max_len, total_len)) != SPR_OK) return st;
@@ -813,14 +828,20 @@ spr_status spr_suffix_attn_bwd_accum(const spr_dims* dims, const void* k_p, cons
                            {gv_cache, P * hkv * hd * 4, "gv_cache", true}};
   if ((st = check_bufs(bufs)) != SPR_OK) return st;
   if ((st = check_ws(ws_layout(SPR_OP_SUFFIX_BWD, dims, n_mb, max_len, total_len), ws, ws_bytes)) != SPR_OK) return st;
+  const SuffixBwdPlan base = suffix_bwd_base_plan(dims, n_mb, max_len);
   SuffixBwdPlan plan = suffix_bwd_plan(dims, n_mb, max_len);
   WsLayout w = suffix_bwd_layout(dims, n_mb, max_len, total_len, plan);
-  if (w.total > ws_bytes) {  // the plan that needs no more than the call insists on
-    plan = suffix_bwd_base_plan(dims, n_mb, max_len);
+  const FillRule rule = suffix_fill_rule(dims, n_mb, max_len, plan.shares);
+  // the plan that needs no more than the call insists on, where the other
+  // does not fit or does not pay
+  if (w.total > ws_bytes || (plan.by_rows && (padded ? gate == nullptr : !fill_pays(rule, total_len)))) {
+    plan = base;
     w = suffix_bwd_layout(dims, n_mb, max_len, total_len, plan);
   }
+  const bool gated = plan.by_rows && padded;
+  const WsLayout wb = suffix_bwd_layout(dims, n_mb, max_len, total_len, base);  // (of the shared launch)
   std::vector<Buf> all = bufs;
-  all.push_back({ws, w.total, "ws", false});
+  all.push_back({ws, gated ? std::max(w.total, wb.total) : w.total, "ws", false});
   if ((st = check_aliasing({bufs[12], bufs[13]}, all)) != SPR_OK) return st;
 
   const bool aq = atomic_dq(dims);
@@ -856,11 +877,7 @@ spr_status spr_suffix_attn_bwd_accum(const spr_dims* dims, const void* k_p, cons
     a.n_split = suffix_bwd_splits(dims, n_mb, max_len);
     if (a.n_split > 1) a.part_dq = at<float>(ws, w.part_dq);
   }
-  a.kv_rsplit = plan.shares;
-  if (a.kv_rsplit > 1) {
-    a.part_dk = at<float>(ws, w.part_dk);
-    a.part_dv = at<float>(ws, w.part_dv);
-  }
+  if (gated && (st = hip_check(launch_fill_gate(rule, cu_seqlens, n_mb, gate, stream), "gate")) != SPR_OK) return st;
   if (plan.wide) {
     // the key-outer role alone on 192-key tiles, then the query-outer role
     // (as Phase C of a long prefix)
@@ -871,21 +888,51 @@ spr_status spr_suffix_attn_bwd_accum(const spr_dims* dims, const void* k_p, cons
     kv.n_split = 1;
     kv.part_dq = nullptr;
     kv.kv_split_prefix_only = plan.fills ? 1 : 0;
+    kv.kv_rsplit = plan.shares;
+    if (plan.shares > 1) {
+      kv.part_dk = at<float>(ws, w.part_dk);
+      kv.part_dv = at<float>(ws, w.part_dv);
+    }
+    if (gated) {
+      kv.gate = gate;
+      kv.gate_value = 1;
+    }
     if ((st = hip_check(launch_bwd_bf16_kv_wide(kv, dims->head_dim, stream), "suffix backward, dK/dV")) != SPR_OK)
       return st;
-    AttnArgs q = a;
-    q.n_prefix_k_tiles = 0;
-    q.n_suffix_k_tiles = 0;
-    q.kv_rsplit = 1;
-    q.part_dk = q.part_dv = nullptr;
-    if ((st = hip_check(launch_bwd(dims, q, n_mb, stream), "suffix backward, dQ")) != SPR_OK) return st;
-  } else if ((st = hip_check(launch_bwd(dims, a, n_mb, stream), "suffix backward")) != SPR_OK) {
-    return st;
   }
+  if (gated) {  // the shared launch; its key-outer blocks run where the launch before did not
+    a.gate = gate;
+    a.gate_value = 0;
+  }
+  if (plan.wide && !gated) {
+    a.n_prefix_k_tiles = 0;
+    a.n_suffix_k_tiles = 0;
+  } else {
+    a.kv_rsplit = base.shares;
+    if (base.shares > 1) {
+      a.part_dk = at<float>(ws, wb.part_dk);
+      a.part_dv = at<float>(ws, wb.part_dv);
+    }
+  }
+  if ((st = hip_check(launch_bwd(dims, a, n_mb, stream), plan.wide ? "suffix backward, dQ" : "suffix backward")) != SPR_OK)
+    return st;
   if (dq_acc && (st = hip_check(launch_convert(dims->dtype, dq_acc, a.scale, nullptr, dq_s,
                                                T * hq * hd, stream), "dq convert")) != SPR_OK)
     return st;
   return ok();
+}
+
+}  // namespace
+
+spr_status spr_suffix_attn_bwd_accum(const spr_dims* dims, const void* k_p, const void* v_p,
+                                     const void* q_s, const void* k_s, const void* v_s,
+                                     const void* o_s, const float* lse_s, const void* do_s,
+                                     const int32_t* cu_seqlens, int32_t n_mb, int32_t max_len,
+                                     int32_t total_len, void* dq_s, void* dk_s, void* dv_s,
+                                     float* gk_cache, float* gv_cache, void* ws, size_t ws_bytes,
+                                     hipStream_t stream) {
+  return suffix_bwd_accum(dims, k_p, v_p, q_s, k_s, v_s, o_s, lse_s, do_s, cu_seqlens, n_mb, max_len, total_len,
+                          dq_s, dk_s, dv_s, gk_cache, gv_cache, ws, ws_bytes, stream, false, nullptr);
 }
 
 // ------------------------------------------------- padded suffix layout
@@ -977,10 +1024,10 @@ spr_status spr_suffix_attn_bwd_accum_padded(const spr_dims* dims, const void* k_
   const RowMove in[] = {{q_s, pq, hq * hd * eb}, {k_s, pk, hkv * hd * eb}, {v_s, pv, hkv * hd * eb},
                         {o_s, po, hq * hd * eb},  {lse_s, plse, hq * 4},      {do_s, pdo, hq * hd * eb}};
   if ((st = hip_check(launch_rows_move(true, in, 6, seq_lens, cu, lens_c, n, s_max, stream), "gather")) != SPR_OK) return st;
-  if ((st = spr_suffix_attn_bwd_accum(dims, k_p, v_p, pq, pk, pv, po, plse, pdo, cu, n, s_max, (int32_t)R, pdq,
-                                      pdk, pdv, gk_cache, gv_cache, at<char>(ws, w.inner),
-                                      std::min(w.inner_bytes, ws_bytes - w.inner),
-                                      stream)) != SPR_OK)
+  int32_t* gate = w.gate != 0 && ws_bytes >= w.total ? at<int32_t>(ws, w.gate) : nullptr;
+  if ((st = suffix_bwd_accum(dims, k_p, v_p, pq, pk, pv, po, plse, pdo, cu, n, s_max, (int32_t)R, pdq, pdk, pdv,
+                             gk_cache, gv_cache, at<char>(ws, w.inner), std::min(w.inner_bytes, ws_bytes - w.inner),
+                             stream, true, gate)) != SPR_OK)
     return st;
   const RowMove out[] = {{pdq, dq_s, hq * hd * eb}, {pdk, dk_s, hkv * hd * eb}, {pdv, dv_s, hkv * hd * eb}};
   if ((st = hip_check(launch_rows_move(false, out, 3, seq_lens, cu, lens_c, n, s_max, stream), "scatter")) != SPR_OK)

@@ -1,0 +1,160 @@
+"""When the suffix backward runs its key-outer role in a launch of its own
+whose rounds the prefix tiles' row shares fill.  The rule is restated here
+from its description; its share count is compared with the library's through
+the workspace sizes, its decision with the launches the library makes (GPU),
+and its claim - the launch keeps its 256 slots busy whatever the lengths - by
+replaying the launch with the true lengths as a list schedule."""
+import heapq
+import sys
+
+import numpy as np
+import pytest
+
+from test_row_share_rule import _causal, _suffix_r, _suffix_ws, _tiles, _wide
+
+SLOTS, TILE_COST, SHARE_STEPS = 256, 8, 128
+
+
+def _shares(hq, hkv, P, n, ml):
+    """R for suffixes of equal length, 0: not this form"""
+    g = hq // hkv
+    steps, longest = g * _tiles(n * ml, 32), g * _tiles(ml, 32)
+    wide = _tiles(P, 192) * steps + n * _causal(ml, g, 192)
+    nt = _tiles(P, 192) * hkv
+    if not _wide(wide, hkv, False) or P == 0 or nt * 100 >= 85 * SLOTS * _tiles(nt, SLOTS):
+        return 0
+    sfx = n * _causal(ml, g, 192) * hkv
+    work, even = sfx + n * _tiles(ml, 192) * hkv * TILE_COST, (nt * steps + sfx) // SLOTS
+    best = None
+    for r in range(1, 9):
+        if steps // r < SHARE_STEPS or 10 * (steps // r) < 9 * longest:
+            break
+        share = _tiles(steps, r) + TILE_COST
+        full, last = divmod(nt * r, SLOTS)
+        rest = (last * share + work) // SLOTS
+        t = full * share + (max(share, rest) if last else rest)
+        if best is None or t < best[0]:
+            best = (t, r)
+    return best[1] if best and 100 * best[0] <= 117 * even else 0
+
+
+def _pays(hq, hkv, P, n, ml, rows, r):
+    g = hq // hkv
+    nt, steps, longest = _tiles(P, 192) * hkv, g * _tiles(rows, 32), g * _tiles(ml, 32)
+    sfx = _causal(ml, g, 192) * (256 * rows // ml) // 256 * hkv
+    work = sfx + (rows // 192 + n) * hkv * TILE_COST
+    share, whole = _tiles(steps, r) + TILE_COST, steps // r
+    full, last = divmod(nt * r, SLOTS)
+    rest = (last * share + work) // SLOTS
+    t = max(full * share + (max(share, rest) if last else rest), full * share + longest + TILE_COST,
+            (nt * r * share + work) // SLOTS + (longest + TILE_COST) // 2)
+    useful = nt * steps + sfx
+    return useful >= 32768 and whole >= SHARE_STEPS and 10 * whole >= 9 * longest and 100 * t * SLOTS <= 125 * useful
+
+
+def _utilisation(hq, hkv, P, lens, r):
+    """of the launch's slots, its blocks started in order on the first free one"""
+    g = hq // hkv
+    jobs = [_tiles(g * _tiles(sum(lens), 32), r) + TILE_COST] * (_tiles(P, 192) * hkv * r)
+    for n in lens:
+        jobs += [g * _tiles(n - k, 32) + TILE_COST for k in range(0, n, 192) for _ in range(hkv)]
+    slots = [0] * SLOTS
+    for j in jobs:
+        heapq.heappush(slots, heapq.heappop(slots) + j)
+    return sum(jobs) / SLOTS / max(slots)
+
+
+def _random_groups(rng, count):
+    log = lambda lo, hi: int(round(np.exp(rng.uniform(np.log(lo), np.log(hi)))))
+    for i in range(count):
+        hq, hkv = ((32, 8), (32, 8), (32, 4), (16, 8), (8, 8))[rng.integers(5)]
+        P, n = log(500, 20000), int(rng.integers(2, 17))
+        if i % 4 == 0:    # one long suffix among short ones
+            lens = [log(50, 400) for _ in range(n - 1)] + [log(800, 2048)]
+        elif i % 4 == 1:  # within a factor of five
+            m = log(150, 2048)
+            lens = [max(1, int(m * rng.uniform(0.2, 1))) for _ in range(n)]
+        else:
+            lens = [log(100, 2048) for _ in range(n)]
+        yield hq, hkv, P, [lens[k] for k in rng.permutation(n)]
+
+
+def test_share_counts_follow_the_rule():
+    from paper_2606_01143_amd import binding as B
+    up = lambda x: -(-x // 256) * 256
+    seen = set()
+    for hq, hkv, P, lens in _random_groups(np.random.default_rng(1), 600):
+        n, ml, T, d = len(lens), max(lens), sum(lens), 128
+        r = _shares(hq, hkv, P, n, ml)
+        base, rb = _suffix_ws(hq, hkv, d, P, n, ml, T, False)
+        fixed = base - (2 * up(rb * (P + T) * hkv * d * 4) if rb > 1 else 0)
+        want = fixed + (2 * up(r * (P + T) * hkv * d * 4) if r > 1 else 0) if r else base
+        assert B.workspace_size(B.OP_SUFFIX_BWD, B.make_dims(hq, hkv, d, P, "bf16"), n, ml, T) == max(want, base)
+        seen.add(r)
+    assert {0, 1, 2, 3, 4} <= seen
+
+
+def test_the_form_keeps_its_slots_busy():
+    taken, refused = [], []
+    for hq, hkv, P, lens in _random_groups(np.random.default_rng(2), 2500):
+        n, ml = len(lens), max(lens)
+        r = _shares(hq, hkv, P, n, ml)
+        if r:
+            u = _utilisation(hq, hkv, P, lens, r)
+            (taken if _pays(hq, hkv, P, n, ml, sum(lens), r) else refused).append(u)
+    assert len(taken) > 100 and min(taken) >= 0.70, (len(taken), min(taken))
+    assert len(refused) > 100 and min(refused) < 0.4  # what the equal-length choice alone would run
+
+
+PACKED = [  # hq, hkv, d, P, lens: taken?
+    (32, 4, 128, 5200, (760, 333, 800, 601, 640, 700), True),
+    (32, 4, 128, 10000, (1500, 1311, 1402), True),
+    (32, 8, 64, 1418, (600, 1000, 900, 800, 700, 950, 600, 1000, 900, 800, 700, 950), True),
+    (32, 4, 64, 687, (105, 1992, 538, 163, 658, 341), False),
+    (32, 4, 128, 1306, (428, 410, 2046, 228, 323), False),
+    (32, 8, 64, 1462, (1595, 319, 329, 374, 146, 164), False),
+]
+
+
+def test_the_listed_groups_have_the_form_for_equal_lengths():
+    for hq, hkv, _, P, lens, taken in PACKED:
+        n, ml = len(lens), max(lens)
+        r = _shares(hq, hkv, P, n, ml)
+        assert r > 0 and _pays(hq, hkv, P, n, ml, sum(lens), r) == taken, (P, lens)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hq,hkv,d,P,lens,taken", PACKED, ids=lambda v: str(v) if isinstance(v, int) else None)
+def test_launches_and_bits(gpu, hq, hkv, d, P, lens, taken):
+    """The launches the suffix backward makes, its outputs on sampled rows and
+    keys, and the padded call's bits, whose choice is made on the device."""
+    from paper_2606_01143_amd import binding as B
+    from paper_2606_01143_amd.group import DeviceGroup
+    from sampled_checks import sampled_errors
+    from synthetic import GroupShape, make_group
+    shape = GroupShape(hq, hkv, d, P, lens, "bf16")
+    sys.stderr.write(f"\n[gpu-case] fill rule {shape}\n")
+    sys.stderr.flush()
+    inp = make_group(shape, seed=6)
+    got = {}
+    for layout in ("packed", "padded"):
+        grp = DeviceGroup(inp, dense=False, layout=layout)
+        grp.run_schedule([(0, shape.n)])
+        if layout == "packed":
+            B.gkv_cache_zero(grp.dims, grp.gk, grp.gv)
+            B.profile_enable(True, "bwd_bf16")
+            try:
+                B.profile_reset()
+                grp._suffix_bwd(0, shape.n, None)
+                assert B.profile_query("bwd_bf16")[1] == (2 if taken else 1)
+            finally:
+                B.profile_enable(False)
+            grp.run_schedule([(0, shape.n)])
+        else:
+            grp.gather_padded_outputs()
+        got[layout] = grp.fetch("schedule")
+        del grp
+    if P < 2000:
+        errs = sampled_errors(inp, got["packed"], np.random.default_rng(0))
+        assert all(v <= 2e-2 for v in errs.values()), errs
+    assert all(np.array_equal(got["packed"][k], got["padded"][k]) for k in got["packed"])
