@@ -309,26 +309,48 @@ SuffixBwdPlan suffix_bwd_base_plan(const spr_dims* d, int32_t n_mb, int32_t max_
 //   Hq 32, Hkv 8, d 128, P = 2775, 1728 among 8 short      not taken: 731, R = 2 846
 //
 // With less work than kKvWideMinSteps (one suffix per microbatch) the launch
-// still pays when its workgroups, prefix and suffix tiles together, fill one
-// round to 70% (the suffix forward running beside it uses the idle CUs) or
-// more rounds to 85%, uncut, and a prefix sweep has kWideLoneSteps steps, so
-// that its loop outweighs the tile's cache update.  Measured there, whole
-// steps in ms (Hq 32, d 128, one suffix per microbatch):
-//   Hkv 8, P = 4096, N = 8 x 512 (78% of a round)   2.54 -> 2.31
-//   Hkv 8, P = 5000, N = 8 x 512 (94%)              2.97 -> 2.76
-//   Hkv 8, P = 3700, N = 4 x 512 (72%)              1.48 -> 1.39
-//   Hkv 4, P = 10500, N = 4 x 700 (92%)             7.00 -> 6.70
-//   Hkv 8, P = 10240, N = 4 x 512 (89% of two)      5.43 -> 5.25
-// and outside: P = 3300 (66%) 1.24 -> 1.29, P = 8192 x 600 (73% of two)
-// 4.15 -> 4.24, P = 4400 x 300 (38 steps) 1.52 -> 1.56, d = 64 even.
+// can still pay, uncut, where its workgroups fill one round to 70% or more
+// rounds to 85% and a prefix sweep has kWideLoneSteps steps (38 steps, P = 4400
+// x 300: a step 1.52 -> 1.56 ms; d = 64 even).  Two things eat the gain: a
+// causal suffix tile is half a sweep on average but holds its CU alone, and the
+// query-outer launch that follows is alone too, with a last round that may be
+// nearly empty.  So both ways are estimated in microseconds, from fits over 292
+// single suffixes (Hq 8-32, Hkv 4 and 8, d 128, P 500-20000, S 160-2048; within
+// 4% and 2.6%), and this one is taken where it gains 1%.
+// Backward calls measured, shared launch -> this launch and the query-outer
+// one: taken on the fill alone, 0.81 to 1.17 times as fast, 119 of 292 slower by
+// over 1.5% (Hq 8, Hkv 8, P = 2403 x 1890 129 -> 153 us; Hq 32, Hkv 8, P = 2685
+// x 1592 377 -> 442); by the estimate 143 of them, 0.97 to 1.17, and whole steps
+// 0.98 to 1.08 times as fast:
+//   Hq 32, Hkv 8, P = 4096 x 512                     170 -> 166 us
+//   Hq 32, Hkv 8, P = 5000 x 512                     201 -> 180
+//   Hq 32, Hkv 4, P = 11602 x 430                    372 -> 319
+//   Hq 32, Hkv 8, P = 19026 x 1927                  2411 -> 2191
+//   Hq 16, Hkv 8, P = 10236 x 964                    367 -> 332
 constexpr long kWideLoneSteps = 48;
 bool suffix_kv_wide_lone(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   if (d->dtype != SPR_BF16 || atomic_dq(d) || d->head_dim != 128 || d->prefix_len == 0 || n_mb != 1 || max_len < 1)
     return false;
-  const long g = d->num_q_heads / d->num_kv_heads, slots = bwd_bf16_kv_wide_slots();
-  const long blocks = (tiles(d->prefix_len, (int)wide_bk()) + tiles(max_len, (int)wide_bk())) * (long)d->num_kv_heads;
-  const long rounds = (blocks + slots - 1) / slots;
-  return g * ((max_len + 31) / 32) >= kWideLoneSteps && blocks * 100 >= (rounds == 1 ? 70 : 85) * slots * rounds;
+  const long g = d->num_q_heads / d->num_kv_heads, hkv = d->num_kv_heads, slots = bwd_bf16_kv_wide_slots();
+  const long n_pre = tiles(d->prefix_len, (int)wide_bk()) * hkv, n_sfx = tiles(max_len, (int)wide_bk()) * hkv;
+  const long steps = g * ((max_len + 31) / 32), rounds = (n_pre + n_sfx + slots - 1) / slots;
+  if (steps < kWideLoneSteps || (n_pre + n_sfx) * 100 < (rounds == 1 ? 70 : 85) * slots * rounds) return false;
+  // this launch's steps per CU (the rounds of prefix tiles, the suffix tiles
+  // beside the last one and after it), and the key tiles of the query-outer
+  // launch's rounds
+  const double sweep = steps + kWideTileCost, full = n_pre / slots * sweep;
+  const double work = causal_steps(max_len, g, wide_bk()) * hkv + n_sfx * kWideTileCost;
+  double key = full + sweep;
+  if (n_pre % slots + n_sfx > slots)
+    key = std::max({key, full + (n_pre % slots * sweep + work) / slots, (n_pre * sweep + work) / slots + sweep / 2});
+  const double pt = tiles(d->prefix_len, bwd_bf16_block_k()), st = tiles(max_len, bwd_bf16_block_k());
+  const long q_blocks = (long)tiles(max_len, bwd_bf16_block_q()) * d->num_q_heads;
+  const int ns = suffix_bwd_splits(d, n_mb, max_len);
+  const double query = (double)((q_blocks * ns + 511) / 512) * ((pt + (st + 2) / 2) / ns + 2);
+  // the shared launch: both roles' work over its 512 slots
+  const double key64 = (pt * steps + causal_steps(max_len, g)) * hkv / 512;
+  const double query64 = q_blocks * (pt + (st + 1) / 2) / 512;
+  return 33.5 + 1.35 * key64 + 2.71 * query64 >= 1.01 * (24 + 1.62 * key + 1.55 * query);
 }
 SuffixBwdPlan suffix_bwd_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   const SuffixBwdPlan base = suffix_bwd_base_plan(d, n_mb, max_len);

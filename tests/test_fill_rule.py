@@ -3,7 +3,9 @@ whose rounds the prefix tiles' row shares fill.  The rule is restated here
 from its description; its share count is compared with the library's through
 the workspace sizes, its decision with the launches the library makes (GPU),
 and its claim - the launch keeps its 256 slots busy whatever the lengths - by
-replaying the launch with the true lengths as a list schedule."""
+replaying the launch with the true lengths as a list schedule.  One suffix per
+microbatch: uncut, by an estimate of both ways' times, which is restated and
+checked the same way."""
 import heapq
 import sys
 
@@ -124,7 +126,7 @@ def test_the_listed_groups_have_the_form_for_equal_lengths():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("hq,hkv,d,P,lens,taken", PACKED, ids=lambda v: str(v) if isinstance(v, int) else None)
+@pytest.mark.parametrize("hq,hkv,d,P,lens,taken", PACKED, ids=[f"hkv{c[1]}_d{c[2]}_p{c[3]}" for c in PACKED])
 def test_launches_and_bits(gpu, hq, hkv, d, P, lens, taken):
     """The launches the suffix backward makes, its outputs on sampled rows and
     keys, and the padded call's bits, whose choice is made on the device."""
@@ -158,3 +160,75 @@ def test_launches_and_bits(gpu, hq, hkv, d, P, lens, taken):
         errs = sampled_errors(inp, got["packed"], np.random.default_rng(0))
         assert all(v <= 2e-2 for v in errs.values()), errs
     assert all(np.array_equal(got["packed"][k], got["padded"][k]) for k in got["packed"])
+
+
+def _lone(hq, hkv, P, S):
+    """one suffix: estimated gain of the key-outer-only launch, 0 outside its range"""
+    g = hq // hkv
+    pre, sfx, steps = _tiles(P, 192) * hkv, _tiles(S, 192) * hkv, g * _tiles(S, 32)
+    rounds = _tiles(pre + sfx, SLOTS)
+    if steps < 48 or (pre + sfx) * 100 < (70 if rounds == 1 else 85) * SLOTS * rounds:
+        return 0
+    sweep, work = steps + TILE_COST, _causal(S, g, 192) * hkv + sfx * TILE_COST
+    full, last = divmod(pre, SLOTS)
+    key = (full + 1) * sweep
+    if last + sfx > SLOTS:
+        key = max(key, full * sweep + (last * sweep + work) / SLOTS, (pre * sweep + work) / SLOTS + sweep / 2)
+    pt, st, blocks = _tiles(P, 64), _tiles(S, 64), _tiles(S, 128) * hq
+    ns = 1 if blocks >= 512 else max(1, min((pt + st) // 16, _tiles(512, blocks), 8))
+    query = _tiles(blocks * ns, 512) * ((pt + (st + 2) / 2) / ns + 2)
+    shared = 33.5 + 1.35 * (pt * steps + _causal(S, g)) * hkv / 512 + 2.71 * blocks * (pt + (st + 1) / 2) / 512
+    return shared / (24 + 1.62 * key + 1.55 * query)
+
+
+LONE = [  # hq, hkv, P, S: taken?
+    (32, 8, 4060, 512, True),     # one 64-key tile of prefix past the line
+    (32, 8, 4032, 512, False),
+    (32, 4, 8737, 161, True),     # 48 steps
+    (32, 4, 8737, 160, False),    # 40
+    (16, 8, 10236, 964, True),    # two rounds
+    (8, 8, 2403, 1890, False),    # 72% of a round by count, half of it by work
+    (32, 8, 2685, 1592, False),
+    (32, 8, 3700, 512, False),
+]
+
+
+def test_one_suffix_fills_its_launch_or_shares():
+    for hq, hkv, P, S, taken in LONE:
+        assert (_lone(hq, hkv, P, S) >= 1.01) == taken, (hq, hkv, P, S)
+    rng = np.random.default_rng(3)
+    log = lambda lo, hi: int(round(np.exp(rng.uniform(np.log(lo), np.log(hi)))))
+    taken, refused = [], []
+    for _ in range(4000):
+        hq, hkv = ((32, 8), (32, 8), (32, 4), (16, 8), (8, 8))[rng.integers(5)]
+        P, S = log(500, 20000), log(100, 2048)
+        gain = _lone(hq, hkv, P, S)
+        if gain:
+            (taken if gain >= 1.01 else refused).append(_utilisation(hq, hkv, P, [S], 1))
+    assert len(taken) > 200 and min(taken) >= 0.70, (len(taken), min(taken))
+    assert len(refused) > 100 and min(refused) < 0.6  # what the count of tiles alone would run
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hq,hkv,P,S,taken", LONE)
+def test_one_suffix_launches(gpu, hq, hkv, P, S, taken):
+    """The launches of the call; both forms' outputs are checked elsewhere."""
+    import torch
+    from paper_2606_01143_amd import binding as B
+    sys.stderr.write(f"\n[gpu-case] fill rule, one suffix {hq, hkv, P, S}\n")
+    sys.stderr.flush()
+    d, dims = 128, B.make_dims(hq, hkv, 128, P, "bf16")
+    bf = lambda *shape: torch.zeros(*shape, dtype=torch.bfloat16, device="cuda")
+    f32 = lambda *shape: torch.zeros(*shape, dtype=torch.float32, device="cuda")
+    kp, vp, gk, gv = bf(P, hkv, d), bf(P, hkv, d), f32(P, hkv, d), f32(P, hkv, d)
+    q, k, v, o, do = bf(S, hq, d), bf(S, hkv, d), bf(S, hkv, d), bf(S, hq, d), bf(S, hq, d)
+    cu = torch.tensor([0, S], dtype=torch.int32, device="cuda")
+    ws = torch.empty(B.workspace_size(B.OP_SUFFIX_BWD, dims, 1, S, S), dtype=torch.uint8, device="cuda")
+    B.profile_enable(True, "bwd_bf16")
+    try:
+        B.profile_reset()
+        B.suffix_attn_bwd_accum(dims, kp, vp, q, k, v, o, f32(S, hq), do, cu, 1, S, S, torch.empty_like(q),
+                                torch.empty_like(k), torch.empty_like(v), gk, gv, ws)
+        assert B.profile_query("bwd_bf16")[1] == (2 if taken else 1)
+    finally:
+        B.profile_enable(False)
