@@ -200,7 +200,7 @@ hipError_t launch_convert(int dtype, const float* acc, float scale, const float*
 // thread adds them in order.
 __global__ __launch_bounds__(kAuxThreads) void seq_offsets_kernel(const int32_t* __restrict__ lens, int n,
                                                                   int s_max, int32_t* __restrict__ cu,
-                                                                  int32_t* __restrict__ lens_c) {
+                                                                  int32_t* __restrict__ lens_c, FillGate gate) {
   __shared__ int32_t chunk[kAuxThreads];
   int32_t run = 0;
   for (int base = 0; base < n; base += kAuxThreads) {
@@ -220,7 +220,10 @@ __global__ __launch_bounds__(kAuxThreads) void seq_offsets_kernel(const int32_t*
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) cu[n] = run;
+  if (threadIdx.x == 0) {
+    cu[n] = run;
+    if (gate.out != nullptr) *gate.out = fill_pays(gate.rule, run) ? 1 : 0;
+  }
 }
 
 // Several tensors' rows in one launch.  Tensor j moves row_units[j] units
@@ -238,13 +241,13 @@ struct RowMoves {
 // With few suffixes (n <= kLdsSeqs) each block derives the offsets itself
 // from the raw lengths (clamped as in seq_offsets_kernel), and block 0 of a
 // gather also stores them to cu_pre / lens_pre for the packed kernels that
-// follow, so no separate offsets launch is needed; otherwise cu / lens_c
-// come precomputed.
+// follow, with the gate of their choice, so no separate offsets launch is
+// needed; otherwise cu / lens_c come precomputed.
 constexpr int kLdsSeqs = 1024;
 __global__ __launch_bounds__(kAuxThreads) void rows_move_kernel(RowMoves m, const int32_t* __restrict__ lens,
                                                                 int n, const int32_t* __restrict__ cu_pre,
                                                                 const int32_t* __restrict__ lens_pre, int s_max,
-                                                                long total, int gather) {
+                                                                long total, int gather, FillGate gate) {
   __shared__ int32_t cu_s[kLdsSeqs + 1], len_s[kLdsSeqs];
   const int32_t *cu = cu_pre, *lens_c = lens_pre;
   if (lens != nullptr) {
@@ -266,6 +269,7 @@ __global__ __launch_bounds__(kAuxThreads) void rows_move_kernel(RowMoves m, cons
       int32_t* len_out = const_cast<int32_t*>(lens_pre);
       for (int i = threadIdx.x; i <= n; i += kAuxThreads) cu_out[i] = cu_s[i];
       for (int i = threadIdx.x; i < n; i += kAuxThreads) len_out[i] = len_s[i];
+      if (gate.out != nullptr && threadIdx.x == 0) *gate.out = fill_pays(gate.rule, cu_s[n]) ? 1 : 0;
     }
   }
   const long idx = (long)blockIdx.x * kAuxThreads + threadIdx.x;
@@ -297,16 +301,16 @@ __global__ __launch_bounds__(kAuxThreads) void rows_move_kernel(RowMoves m, cons
 }
 
 hipError_t launch_seq_offsets(const int32_t* lens, int n, int s_max, int32_t* cu, int32_t* lens_c,
-                              hipStream_t st) {
+                              hipStream_t st, const FillGate& gate) {
   ProfileScope ps("seq_offsets", st);
-  hipLaunchKernelGGL(seq_offsets_kernel, dim3(1), dim3(kAuxThreads), 0, st, lens, n, s_max, cu, lens_c);
+  hipLaunchKernelGGL(seq_offsets_kernel, dim3(1), dim3(kAuxThreads), 0, st, lens, n, s_max, cu, lens_c, gate);
   return hipGetLastError();
 }
 
 bool rows_move_needs_offsets(int n) { return n > kLdsSeqs; }
 
 hipError_t launch_rows_move(bool gather, const RowMove* moves, int count, const int32_t* lens, const int32_t* cu,
-                            const int32_t* lens_c, int n, int s_max, hipStream_t st) {
+                            const int32_t* lens_c, int n, int s_max, hipStream_t st, const FillGate& gate) {
   if (count < 1 || count > kMaxRowMoves) return hipErrorInvalidValue;
   RowMoves m;
   m.count = count;
@@ -332,7 +336,7 @@ hipError_t launch_rows_move(bool gather, const RowMove* moves, int count, const 
   const unsigned nb = (unsigned)((total + kAuxThreads - 1) / kAuxThreads);
   ProfileScope ps(gather ? "rows_gather" : "rows_scatter", st);
   hipLaunchKernelGGL(rows_move_kernel, dim3(nb), dim3(kAuxThreads), 0, st, m, n <= kLdsSeqs ? lens : nullptr, n,
-                     cu, lens_c, s_max, total, gather ? 1 : 0);
+                     cu, lens_c, s_max, total, gather ? 1 : 0, gate);
   return hipGetLastError();
 }
 

@@ -1091,18 +1091,6 @@ hipError_t launch_bwd_bf16(const AttnArgs& a, int head_dim, int n_qz, bool deter
 
 int bwd_bf16_block_q() { return kQBQ; }
 
-namespace {
-__global__ void fill_gate_kernel(FillRule r, const int32_t* cu, int n, int32_t* gate) {
-  if (threadIdx.x == 0) *gate = fill_pays(r, cu[n]) ? 1 : 0;
-}
-}  // namespace
-
-hipError_t launch_fill_gate(const FillRule& r, const int32_t* cu, int n, int32_t* gate, hipStream_t st) {
-  ProfileScope ps("fill_gate", st);
-  hipLaunchKernelGGL(fill_gate_kernel, dim3(1), dim3(64), 0, st, r, cu, n, gate);
-  return hipGetLastError();
-}
-
 int bwd_bf16_kvsplit(long kv_tiles, long max_tiles, bool kv_alone, int slots) {
   // kv_tiles: the key-outer role's (32-row tile, q head) steps over all its
   // blocks; max_tiles: the longest block's.  The query-outer role adds about

@@ -109,8 +109,12 @@ __host__ __device__ inline bool fill_pays(const FillRule& r, long rows) {
   return useful >= kKvWideMinSteps && whole >= kWideShareSteps && 10 * whole >= 9 * longest &&
          100 * t * r.slots <= 125 * useful;
 }
-// *gate = fill_pays(r, cu[n]) as 0 or 1
-hipError_t launch_fill_gate(const FillRule& r, const int32_t* cu, int n, int32_t* gate, hipStream_t st);
+// where the rows are known on the device only: *out = fill_pays(rule, rows) as
+// 0 or 1, written by the launch that adds up the lengths (null: not asked for)
+struct FillGate {
+  FillRule rule;
+  int32_t* out;
+};
 
 int f32_block_q();
 int f32_block_k();
@@ -136,18 +140,19 @@ hipError_t launch_accumulate(float* dst, const float* src, size_t n, hipStream_t
 // padded suffix layout: cu/lens_c from device lengths, and row gather
 // (padded -> packed) or scatter (packed -> padded, padding rows zeroed)
 hipError_t launch_seq_offsets(const int32_t* lens, int n, int s_max, int32_t* cu, int32_t* lens_c,
-                              hipStream_t st);
+                              hipStream_t st, const FillGate& gate = {});
 constexpr int kMaxRowMoves = 6;
 struct RowMove {
   const void* src;
   void* dst;
   size_t row_bytes;  // a multiple of 4
 };
-// few suffixes: the move kernels derive the offsets from `lens` themselves;
-// many: cu / lens_c must come from launch_seq_offsets first
+// few suffixes: the move kernels derive the offsets (and a gather's gate) from
+// `lens` themselves; many: they must come from launch_seq_offsets first
 bool rows_move_needs_offsets(int n);
 hipError_t launch_rows_move(bool gather, const RowMove* moves, int count, const int32_t* lens,
-                            const int32_t* cu, const int32_t* lens_c, int n, int s_max, hipStream_t st);
+                            const int32_t* cu, const int32_t* lens_c, int n, int s_max, hipStream_t st,
+                            const FillGate& gate = {});
 
 // decoder-layer token-wise operations (kernels_layer.hip)
 hipError_t launch_rmsnorm_fwd(int rows, int width, float eps, const void* x, void* y, float* rstd,

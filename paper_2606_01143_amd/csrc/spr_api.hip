@@ -821,7 +821,8 @@ spr_status spr_check_cu_seqlens(const int32_t* cu_host, int32_t n_mb, int32_t ma
 
 namespace {
 // `padded`: total_len bounds the rows, which only the device knows, and a
-// choice that depends on them goes through `gate` (null: no room for it)
+// choice that depends on them is in `gate`, written by the launch that added
+// up the lengths (null: no room for it)
 spr_status suffix_bwd_accum(const spr_dims* dims, const void* k_p, const void* v_p,
                             const void* q_s, const void* k_s, const void* v_s,
                             const void* o_s, const float* lse_s, const void* do_s,
@@ -899,7 +900,6 @@ spr_status suffix_bwd_accum(const spr_dims* dims, const void* k_p, const void* v
     a.n_split = suffix_bwd_splits(dims, n_mb, max_len);
     if (a.n_split > 1) a.part_dq = at<float>(ws, w.part_dq);
   }
-  if (gated && (st = hip_check(launch_fill_gate(rule, cu_seqlens, n_mb, gate, stream), "gate")) != SPR_OK) return st;
   if (plan.wide) {
     // the key-outer role alone on 192-key tiles, then the query-outer role
     // (as Phase C of a long prefix)
@@ -1040,16 +1040,19 @@ spr_status spr_suffix_attn_bwd_accum_padded(const spr_dims* dims, const void* k_
   float* plse = at<float>(ws, w.plse);
   // the offsets in workspace, for the packed calls: written by the gather
   // itself unless there are too many suffixes for it
+  FillGate gate{};
+  if (w.gate != 0 && ws_bytes >= w.total)
+    gate = {suffix_fill_rule(dims, n, s_max, suffix_bwd_plan(dims, n, s_max).shares), at<int32_t>(ws, w.gate)};
   if (rows_move_needs_offsets(n) &&
-      (st = hip_check(launch_seq_offsets(seq_lens, n, s_max, cu, lens_c, stream), "offsets")) != SPR_OK)
+      (st = hip_check(launch_seq_offsets(seq_lens, n, s_max, cu, lens_c, stream, gate), "offsets")) != SPR_OK)
     return st;
   const RowMove in[] = {{q_s, pq, hq * hd * eb}, {k_s, pk, hkv * hd * eb}, {v_s, pv, hkv * hd * eb},
                         {o_s, po, hq * hd * eb},  {lse_s, plse, hq * 4},      {do_s, pdo, hq * hd * eb}};
-  if ((st = hip_check(launch_rows_move(true, in, 6, seq_lens, cu, lens_c, n, s_max, stream), "gather")) != SPR_OK) return st;
-  int32_t* gate = w.gate != 0 && ws_bytes >= w.total ? at<int32_t>(ws, w.gate) : nullptr;
+  if ((st = hip_check(launch_rows_move(true, in, 6, seq_lens, cu, lens_c, n, s_max, stream, gate), "gather")) != SPR_OK)
+    return st;
   if ((st = suffix_bwd_accum(dims, k_p, v_p, pq, pk, pv, po, plse, pdo, cu, n, s_max, (int32_t)R, pdq, pdk, pdv,
                              gk_cache, gv_cache, at<char>(ws, w.inner), std::min(w.inner_bytes, ws_bytes - w.inner),
-                             stream, true, gate)) != SPR_OK)
+                             stream, true, gate.out)) != SPR_OK)
     return st;
   const RowMove out[] = {{pdq, dq_s, hq * hd * eb}, {pdk, dk_s, hkv * hd * eb}, {pdv, dv_s, hkv * hd * eb}};
   if ((st = hip_check(launch_rows_move(false, out, 3, seq_lens, cu, lens_c, n, s_max, stream), "scatter")) != SPR_OK)

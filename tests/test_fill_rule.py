@@ -108,6 +108,7 @@ def test_the_form_keeps_its_slots_busy():
     assert len(refused) > 100 and min(refused) < 0.4  # what the equal-length choice alone would run
 
 
+MANY = tuple(2 + 7 * i % 29 for i in range(1100))  # more lengths than a gather block adds up
 PACKED = [  # hq, hkv, d, P, lens: taken?
     (32, 4, 128, 5200, (760, 333, 800, 601, 640, 700), True),
     (32, 4, 128, 10000, (1500, 1311, 1402), True),
@@ -115,6 +116,8 @@ PACKED = [  # hq, hkv, d, P, lens: taken?
     (32, 4, 64, 687, (105, 1992, 538, 163, 658, 341), False),
     (32, 4, 128, 1306, (428, 410, 2046, 228, 323), False),
     (32, 8, 64, 1462, (1595, 319, 329, 374, 146, 164), False),
+    (32, 4, 64, 1800, MANY, True),
+    (32, 4, 64, 1500, MANY, False),
 ]
 
 
@@ -156,7 +159,7 @@ def test_launches_and_bits(gpu, hq, hkv, d, P, lens, taken):
             grp.gather_padded_outputs()
         got[layout] = grp.fetch("schedule")
         del grp
-    if P < 2000:
+    if P < 2000 and len(lens) < 100:
         errs = sampled_errors(inp, got["packed"], np.random.default_rng(0))
         assert all(v <= 2e-2 for v in errs.values()), errs
     assert all(np.array_equal(got["packed"][k], got["padded"][k]) for k in got["packed"])
