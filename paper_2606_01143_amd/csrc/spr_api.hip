@@ -296,10 +296,13 @@ SuffixBwdPlan suffix_bwd_base_plan(const spr_dims* d, int32_t n_mb, int32_t max_
 // shorter, and the longest suffix's tiles, uncut and last, would end the
 // launch alone.  Packed calls know the rows on the host; padded calls decide
 // on the device, between this launch and the shared one's key-outer blocks.
+// The blocks that leave cost them 5 to 7 us, so sizes at which equal lengths
+// do not pay have no R (Hq 32, Hkv 4, d 64, P = 3577, five up to 489: 401 us
+// shared, 408 with the choice; of 4000 drawn groups none paid with fewer rows).
 //
 // Suffix backward calls measured, shared launch / this, on 950 packed groups
 // (Hq 8-32, Hkv 4 and 8, d 64 and 128, P 500-20000, 2 to 16 suffixes of up to
-// 2048, equal, drawn, and one long among short): 486 have an R, and of the 373
+// 2048, equal, drawn, and one long among short): 486 are within the 17%, and of the 373
 // unequal ones among them 184 would be slower, down to 0.43. fill_pays takes
 // 116, at 0.99 to 2.16, geometric mean 1.19, and none of the 184; the launch
 // keeps at least 70% of its slots busy there.  Examples in us:
@@ -352,6 +355,11 @@ bool suffix_kv_wide_lone(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   const double query64 = q_blocks * (pt + (st + 1) / 2) / 512;
   return 33.5 + 1.35 * key64 + 2.71 * query64 >= 1.01 * (24 + 1.62 * key + 1.55 * query);
 }
+FillRule suffix_fill_rule(const spr_dims* d, int32_t n_mb, int32_t max_len, int shares) {
+  const long g = d->num_q_heads / d->num_kv_heads, hkv = d->num_kv_heads;
+  return {(long)tiles(d->prefix_len, (int)wide_bk()) * hkv, g, hkv, n_mb, max_len,
+          causal_steps(max_len, g, wide_bk()), shares, bwd_bf16_kv_wide_slots()};
+}
 SuffixBwdPlan suffix_bwd_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   const SuffixBwdPlan base = suffix_bwd_base_plan(d, n_mb, max_len);
   if (!base.wide && base.shares == 1 && suffix_kv_wide_lone(d, n_mb, max_len)) return {true, 1, true, false};
@@ -376,13 +384,10 @@ SuffixBwdPlan suffix_bwd_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) 
       best = t;
     }
   }
-  if (best_r == 0 || 100 * best > 117 * even) return base;
+  if (best_r == 0 || 100 * best > 117 * even ||
+      !fill_pays(suffix_fill_rule(d, n_mb, max_len, (int)best_r), (long)n_mb * max_len))
+    return base;
   return {true, (int)best_r, true, true};
-}
-FillRule suffix_fill_rule(const spr_dims* d, int32_t n_mb, int32_t max_len, int shares) {
-  const long g = d->num_q_heads / d->num_kv_heads, hkv = d->num_kv_heads;
-  return {(long)tiles(d->prefix_len, (int)wide_bk()) * hkv, g, hkv, n_mb, max_len,
-          causal_steps(max_len, g, wide_bk()), shares, bwd_bf16_kv_wide_slots()};
 }
 // Phase C: causal prefix rows; key tile 0 sweeps all P
 int prefix_bwd_kv_splits(const spr_dims* d) {

@@ -37,7 +37,7 @@ def _shares(hq, hkv, P, n, ml):
         t = full * share + (max(share, rest) if last else rest)
         if best is None or t < best[0]:
             best = (t, r)
-    return best[1] if best and 100 * best[0] <= 117 * even else 0
+    return best[1] if best and 100 * best[0] <= 117 * even and _pays(hq, hkv, P, n, ml, n * ml, best[1]) else 0
 
 
 def _pays(hq, hkv, P, n, ml, rows, r):
@@ -116,16 +116,21 @@ PACKED = [  # hq, hkv, d, P, lens: taken?
     (32, 4, 64, 687, (105, 1992, 538, 163, 658, 341), False),
     (32, 4, 128, 1306, (428, 410, 2046, 228, 323), False),
     (32, 8, 64, 1462, (1595, 319, 329, 374, 146, 164), False),
+    (32, 8, 64, 1608, (214, 135, 1588, 1744, 371, 147), False),
+    (32, 8, 128, 1846, (166, 1882, 1309, 136, 1420, 603), False),
     (32, 4, 64, 1800, MANY, True),
     (32, 4, 64, 1500, MANY, False),
 ]
 
 
-def test_the_listed_groups_have_the_form_for_equal_lengths():
+def test_the_listed_groups_take_the_form_or_not():
+    refused = 0
     for hq, hkv, _, P, lens, taken in PACKED:
         n, ml = len(lens), max(lens)
         r = _shares(hq, hkv, P, n, ml)
-        assert r > 0 and _pays(hq, hkv, P, n, ml, sum(lens), r) == taken, (P, lens)
+        assert (r > 0 and _pays(hq, hkv, P, n, ml, sum(lens), r)) == taken, (P, lens)
+        refused += r > 0 and not taken
+    assert refused >= 3  # a choice that padded calls make on the device
 
 
 @pytest.mark.gpu
