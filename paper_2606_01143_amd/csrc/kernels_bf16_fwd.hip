@@ -501,7 +501,7 @@ int fwd_bf16_pack_split(int hq, int hkv, int n_mb, int max_len, int prefix_len) 
   // One split (the suffix's own keys with the prefix) where the suffixes'
   // tiles give every CU two workgroups; else the prefix keys in as many
   // ranges of at least four 64-key tiles as make about two workgroups per
-  // CU, plus one.  The partials then stay below 512 tiles of fp32 rows.
+  // CU, plus one.
   // Writing and merging a range's partials costs as much as sweeping about
   // half a tile, so ranges of at most eight tiles (512 keys), 16 and more of
   // them, are cut for 384 workgroups instead: two workgroups per CU -> this,
@@ -514,8 +514,42 @@ int fwd_bf16_pack_split(int hq, int hkv, int n_mb, int max_len, int prefix_len) 
   if (tiles >= 512 || prefix_len < 4 * kTileRows) return 1;
   const long all = ((long)n_mb * max_len * (hq / hkv) + kFwdBQ - 1) / kFwdBQ * hkv;
   const long fewer = std::max({384 / all, 16L, (long)prefix_len / (8 * kTileRows)});
-  const long ns = std::min({512 / all, fewer, (long)prefix_len / (4 * kTileRows)});
-  return (int)std::max(1L, std::min(ns, 32L)) + 1;
+  long ranges = std::min({512 / all, fewer, (long)prefix_len / (4 * kTileRows), 31L});
+  // What follows keeps the form where it wins (some 700 suffix microbatches of P
+  // 250-20000 measured, one to nine suffixes).  One range is the whole prefix
+  // in one sweep, and saves only the own keys' tiles: less than the merge costs
+  // on a short prefix, which is then not split (few row blocks: the one-head
+  // form), and half of what two ranges save on a long one.  One range / this,
+  // us: Hq 32, Hkv 8, d 64, P = 500, three up to 156 17.3 / 13.8; d 128, P =
+  // 282, five up to 192 28.1 / 15.9, P = 908, six up to 262 37.6 / 28.1; Hkv 4,
+  // P = 4579, four up to 286 92.5 / 58.6 (one-head 76.9).  Around the line, P =
+  // 1473 and 1865, not split / two ranges 36.0 / 39.0 and 59.0 / 45.3.
+  const long row_blocks = (max_len + kFwdBQ - 1) / kFwdBQ * (long)hq * n_mb;
+  if (ranges <= 1) return prefix_len >= 1536 ? 3 : row_blocks > 256 ? 1 : 0;
+  // Several suffixes of more than a row tile: ranges of at most eight tiles
+  // leave no workgroup of the launch to a second round (Hq 32, Hkv 8, d 64, P =
+  // 1662, two up to 162: 21.3 -> 18.9).  (Of shorter ones the longest says
+  // little about the rows: P = 1799, six up to 63, four ranges instead of five
+  // 14.8 -> 15.8.)
+  auto tiles_of = [&](long n) { return ((prefix_len + kTileRows - 1) / kTileRows + n - 1) / n; };
+  if (max_len > kFwdBQ && n_mb > 1 && ranges > 2 && tiles_of(ranges) <= 8)
+    ranges = std::min(ranges, std::max(2L, (512 - tiles) / all));
+  // Packing shortens the sweep of a workgroup (more ranges), or gives one or
+  // two waves' rows of a one-head workgroup to full ones.  Where the one-head
+  // form's key splits are as short, over 32 rows fill two of its waves and each
+  // of its workgroups has a CU to itself, or its row tiles are full to 70% and
+  // two share a CU, it is the faster one: Hq 32, Hkv 8, d 128, P = 1113, two up
+  // to 38 15.5 -> 14.2; Hkv 4, d 64, P = 2210, one of 181 21.5 -> 20.1; on the
+  // other side P = 1038, four up to 48 (512 workgroups) packed 15.6, one-head
+  // 16.9, and Hq 16, P = 2558, one of 150 (59% full) 20.9 and 26.4.
+  const int row_splits = fwd_bf16_split((int)row_blocks, prefix_len);
+  const long row_wgs = row_blocks * row_splits;
+  const long row_tiles = (tiles_of(1) + (max_len + kTileRows - 1) / kTileRows + row_splits - 1) / row_splits;
+  const bool full = 10L * max_len >= 7L * kFwdBQ * ((max_len + kFwdBQ - 1) / kFwdBQ);
+  if (max_len > kFwdBQ ? full && ranges <= row_splits && row_wgs <= 512
+                       : max_len > 32 && row_tiles <= tiles_of(ranges) && row_wgs >= 96 && row_wgs <= 256)
+    return 0;
+  return (int)ranges + 1;
 }
 
 }  // namespace spr

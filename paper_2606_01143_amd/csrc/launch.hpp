@@ -61,7 +61,8 @@ int fwd_bf16_split(int n_row_blocks, int prefix_len);
 // taken where that is at most 3/4 of the one-head form's (short suffixes, or
 // lengths just past a multiple of 128); 0: the one-head form
 long fwd_bf16_pack_tiles(int hq, int hkv, int max_len);
-// its key splits: 1, or the prefix key ranges plus one for the suffixes' own
+// its key splits: 1, or the prefix key ranges plus one for the suffixes' own;
+// 0: the one-head form is the faster one
 int fwd_bf16_pack_split(int hq, int hkv, int n_mb, int max_len, int prefix_len);
 int bwd_bf16_block_k();
 // key-outer role alone with six wave pairs (192 keys) per workgroup, one

@@ -428,9 +428,9 @@ hipError_t launch_forward(const spr_dims* d, AttnArgs a, bool prefix, int32_t ma
     a.n_suffix_q_tiles = (int)sw;
     return launch_fwd_bf16_wide(a, d->head_dim, n_z, st);
   }
-  if (!prefix && d->dtype == SPR_BF16) {
+  if (!prefix && suffix_fwd_pack_splits(d, n_z, max_len) > 0) {
     a.n_suffix_q_tiles = (int)fwd_bf16_pack_tiles(d->num_q_heads, d->num_kv_heads, max_len);
-    if (a.n_suffix_q_tiles > 0) return launch_fwd_bf16_pack(a, d->head_dim, n_z, st);
+    return launch_fwd_bf16_pack(a, d->head_dim, n_z, st);
   }
   const int q = block_q(d->dtype);
   a.n_prefix_q_tiles = prefix ? tiles(d->prefix_len, q) : 0;

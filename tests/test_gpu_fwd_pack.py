@@ -54,8 +54,39 @@ def test_split_counts(hq, hkv, d, P, n, ml, splits):
     got = B.workspace_size(B.OP_SUFFIX_FWD, B.make_dims(hq, hkv, d, P, "bf16"), n, ml, T)
     assert got == up(splits * T * hq * d * 4) + up(splits * T * hq * 4)
 
+
+
+@pytest.mark.parametrize("hq,hkv,d,P,n,ml,splits", [
+    (32, 8, 64, 500, 3, 156, 1),      # one range would only add a merge
+    (32, 8, 128, 282, 5, 192, 1),
+    (32, 8, 128, 908, 6, 262, 1),
+    (32, 4, 128, 2136, 4, 267, 3),    # from 1536 keys on there are two
+    (32, 4, 128, 2136, 5, 280, 2),    # (three splits would not fit the static scratch)
+    (32, 8, 128, 1113, 2, 38, 4),     # the one-head form's splits: as short, a CU each
+    (32, 8, 128, 1038, 4, 48, 5),     # two of its workgroups per CU: packed
+    (32, 4, 64, 2210, 1, 181, 8),     # as many, its row tiles 70% full
+    (16, 8, 128, 2558, 1, 150, 10),   # 59% full: packed
+    (32, 8, 64, 1799, 6, 63, 6),
+    (32, 8, 64, 1662, 2, 162, 5),     # five ranges and the own keys would need a second round
+])
+def test_split_counts_of_short_prefixes(hq, hkv, d, P, n, ml, splits):
+    from paper_2606_01143_amd import binding as B
+    up = lambda x: -(-x // 256) * 256
+    T = n * ml
+    got = B.workspace_size(B.OP_SUFFIX_FWD, B.make_dims(hq, hkv, d, P, "bf16"), n, ml, T)
+    assert got == (up(splits * T * hq * d * 4) + up(splits * T * hq * 4) if splits > 1 else 0)
+
+
+SHORT_PREFIX = [
+    GroupShape(32, 8, 128, 282, (192, 150, 130, 70, 69), "bf16"),  # packed, unsplit
+    GroupShape(32, 8, 64, 500, (156, 120, 132), "bf16"),           # one-head
+    GroupShape(32, 8, 128, 1113, (38, 2), "bf16"),                 # one-head, split
+    GroupShape(32, 8, 64, 1662, (162, 80), "bf16"),
+]
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", CASES, ids=lambda s: f"hq{s.num_q_heads}_hkv{s.num_kv_heads}_d{s.head_dim}"
+@pytest.mark.parametrize("shape", CASES + SHORT_PREFIX, ids=lambda s: f"hq{s.num_q_heads}_hkv{s.num_kv_heads}_d{s.head_dim}"
                                                        f"_p{s.prefix_len}_n{s.n}_max{max(s.suffix_lens)}")
 def test_packed_rows_match_oracle(gpu, shape):
     from paper_2606_01143_amd.group import DeviceGroup
