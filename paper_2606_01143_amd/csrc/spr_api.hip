@@ -296,20 +296,23 @@ SuffixBwdPlan suffix_bwd_base_plan(const spr_dims* d, int32_t n_mb, int32_t max_
 // shorter, and the longest suffix's tiles, uncut and last, would end the
 // launch alone.  Packed calls know the rows on the host; padded calls decide
 // on the device, between this launch and the shared one's key-outer blocks.
-// The blocks that leave cost them 5 to 7 us, so sizes at which equal lengths
-// do not pay have no R (Hq 32, Hkv 4, d 64, P = 3577, five up to 489: 401 us
-// shared, 408 with the choice; of 4000 drawn groups none paid with fewer rows).
+// The blocks that leave cost them 5 to 7 us (Hq 32, Hkv 4, d 64, P = 3577, five
+// up to 489: 401 us shared, 408 with the choice), so sizes at which equal
+// lengths do not pay have no R.
 //
-// Suffix backward calls measured, shared launch / this, on 950 packed groups
-// (Hq 8-32, Hkv 4 and 8, d 64 and 128, P 500-20000, 2 to 16 suffixes of up to
-// 2048, equal, drawn, and one long among short): 486 are within the 17%, and of the 373
-// unequal ones among them 184 would be slower, down to 0.43. fill_pays takes
-// 116, at 0.99 to 2.16, geometric mean 1.19, and none of the 184; the launch
-// keeps at least 70% of its slots busy there.  Examples in us:
-//   Hq 32, Hkv 8, d 64,  P = 1418, 16 x 1836               6000 -> 2776
-//   Hq 32, Hkv 8, d 128, P = 1590, 10 x 1834               4198 -> 2714
-//   Hq 32, Hkv 4, d 128, P = 508, 1315 among 10 short      not taken: 196, R = 8 460
-//   Hq 32, Hkv 8, d 128, P = 2775, 1728 among 8 short      not taken: 731, R = 2 846
+// Suffix backward calls measured, shared launch / this, on 700 packed groups
+// within the 17% (Hq 8-32, Hkv 4 and 8, d 64 and 128, P 500-16000, 2 to 16
+// suffixes of up to 2048, equal, near, drawn, and one long among short): taken
+// wherever equal lengths would be, 0.75 to 1.8 times as fast.  fill_pays takes
+// 544, geometric mean 1.23, five below 0.98 (0.945 at least); the 156 that it
+// leaves hold 91 over 1.05, long prefixes with d = 128, where 0.75 to 1.2 lie
+// close together.  With one limit of 1.25 it took 351 and left gains of 1.1 to
+// 1.8.  Examples in us:
+//   Hq 32, Hkv 8, d 128, P = 2048, 4 x 1024                  755 ->  669
+//   Hq 32, Hkv 4, d 64,  P = 4255, 10 x 440                 1514 ->  846
+//   Hq 32, Hkv 8, d 128, P = 1143, 13 of 105 to 1991        2237 -> 1272
+//   Hq 32, Hkv 4, d 128, P = 2162, 5 of 132 to 653           not taken: 338, R = 5  451
+//   Hq 32, Hkv 4, d 128, P = 5404, 6 of 119 to 1010          not taken: 840, R = 2 1025
 //
 // With less work than kKvWideMinSteps (one suffix per microbatch) the launch
 // can still pay, uncut, where its workgroups fill one round to 70% or more
@@ -358,7 +361,7 @@ bool suffix_kv_wide_lone(const spr_dims* d, int32_t n_mb, int32_t max_len) {
 FillRule suffix_fill_rule(const spr_dims* d, int32_t n_mb, int32_t max_len, int shares) {
   const long g = d->num_q_heads / d->num_kv_heads, hkv = d->num_kv_heads;
   return {(long)tiles(d->prefix_len, (int)wide_bk()) * hkv, g, hkv, n_mb, max_len,
-          causal_steps(max_len, g, wide_bk()), shares, bwd_bf16_kv_wide_slots()};
+          causal_steps(max_len, g, wide_bk()), shares, bwd_bf16_kv_wide_slots(), d->head_dim};
 }
 SuffixBwdPlan suffix_bwd_plan(const spr_dims* d, int32_t n_mb, int32_t max_len) {
   const SuffixBwdPlan base = suffix_bwd_base_plan(d, n_mb, max_len);

@@ -17,7 +17,7 @@ from test_row_share_rule import _causal, _suffix_r, _suffix_ws, _tiles, _wide
 SLOTS, TILE_COST, SHARE_STEPS = 256, 8, 128
 
 
-def _shares(hq, hkv, P, n, ml):
+def _shares(hq, hkv, P, n, ml, d=128):
     """R for suffixes of equal length, 0: not this form"""
     g = hq // hkv
     steps, longest = g * _tiles(n * ml, 32), g * _tiles(ml, 32)
@@ -37,10 +37,10 @@ def _shares(hq, hkv, P, n, ml):
         t = full * share + (max(share, rest) if last else rest)
         if best is None or t < best[0]:
             best = (t, r)
-    return best[1] if best and 100 * best[0] <= 117 * even and _pays(hq, hkv, P, n, ml, n * ml, best[1]) else 0
+    return best[1] if best and 100 * best[0] <= 117 * even and _pays(hq, hkv, P, n, ml, n * ml, best[1], d) else 0
 
 
-def _pays(hq, hkv, P, n, ml, rows, r):
+def _pays(hq, hkv, P, n, ml, rows, r, d=128):
     g = hq // hkv
     nt, steps, longest = _tiles(P, 192) * hkv, g * _tiles(rows, 32), g * _tiles(ml, 32)
     sfx = _causal(ml, g, 192) * (256 * rows // ml) // 256 * hkv
@@ -51,7 +51,8 @@ def _pays(hq, hkv, P, n, ml, rows, r):
     t = max(full * share + (max(share, rest) if last else rest), full * share + longest + TILE_COST,
             (nt * r * share + work) // SLOTS + (longest + TILE_COST) // 2)
     useful = nt * steps + sfx
-    return useful >= 32768 and whole >= SHARE_STEPS and 10 * whole >= 9 * longest and 100 * t * SLOTS <= 125 * useful
+    limit = 160 if rows == n * ml else 150 if d == 64 else 144 if _tiles(P, 192) <= 13 else 125
+    return useful >= 32768 and whole >= SHARE_STEPS and 10 * whole >= 9 * longest and 100 * t * SLOTS <= limit * useful
 
 
 def _utilisation(hq, hkv, P, lens, r):
@@ -85,9 +86,9 @@ def test_share_counts_follow_the_rule():
     from paper_2606_01143_amd import binding as B
     up = lambda x: -(-x // 256) * 256
     seen = set()
-    for hq, hkv, P, lens in _random_groups(np.random.default_rng(1), 600):
-        n, ml, T, d = len(lens), max(lens), sum(lens), 128
-        r = _shares(hq, hkv, P, n, ml)
+    for i, (hq, hkv, P, lens) in enumerate(_random_groups(np.random.default_rng(1), 600)):
+        n, ml, T, d = len(lens), max(lens), sum(lens), (128, 64)[i % 2]
+        r = _shares(hq, hkv, P, n, ml, d)
         base, rb = _suffix_ws(hq, hkv, d, P, n, ml, T, False)
         fixed = base - (2 * up(rb * (P + T) * hkv * d * 4) if rb > 1 else 0)
         want = fixed + (2 * up(r * (P + T) * hkv * d * 4) if r > 1 else 0) if r else base
@@ -97,15 +98,16 @@ def test_share_counts_follow_the_rule():
 
 
 def test_the_form_keeps_its_slots_busy():
-    taken, refused = [], []
-    for hq, hkv, P, lens in _random_groups(np.random.default_rng(2), 2500):
-        n, ml = len(lens), max(lens)
-        r = _shares(hq, hkv, P, n, ml)
-        if r:
-            u = _utilisation(hq, hkv, P, lens, r)
-            (taken if _pays(hq, hkv, P, n, ml, sum(lens), r) else refused).append(u)
-    assert len(taken) > 100 and min(taken) >= 0.70, (len(taken), min(taken))
-    assert len(refused) > 100 and min(refused) < 0.4  # what the equal-length choice alone would run
+    for d, long, bound in ((128, True, 0.70), (128, False, 0.58), (64, True, 0.57), (64, False, 0.57)):
+        taken, refused = [], []
+        for hq, hkv, P, lens in _random_groups(np.random.default_rng(2), 2500):
+            n, ml = len(lens), max(lens)
+            r = _shares(hq, hkv, P, n, ml, d)
+            if r and (P > 13 * 192) == long:
+                u = _utilisation(hq, hkv, P, lens, r)
+                (taken if _pays(hq, hkv, P, n, ml, sum(lens), r, d) else refused).append(u)
+        assert len(taken) > 100 and min(taken) >= bound, (d, long, len(taken), min(taken))
+        assert len(refused) > 100 and min(refused) < 0.5  # what the equal-length choice alone would run
 
 
 MANY = tuple(2 + 7 * i % 29 for i in range(1100))  # more lengths than a gather block adds up
@@ -117,18 +119,20 @@ PACKED = [  # hq, hkv, d, P, lens: taken?
     (32, 4, 128, 1306, (428, 410, 2046, 228, 323), False),
     (32, 8, 64, 1462, (1595, 319, 329, 374, 146, 164), False),
     (32, 8, 64, 1608, (214, 135, 1588, 1744, 371, 147), False),
-    (32, 8, 128, 1846, (166, 1882, 1309, 136, 1420, 603), False),
+    (32, 8, 128, 1846, (166, 1882, 1309, 136, 1420, 603), True),
+    (32, 8, 128, 1075, (154, 2003, 121, 56, 63), False),
+    (32, 8, 128, 2048, (1024,) * 4, True),
     (32, 4, 64, 1800, MANY, True),
-    (32, 4, 64, 1500, MANY, False),
+    (16, 4, 64, 1600, (1, 2) * 550 + (40,), False),
 ]
 
 
 def test_the_listed_groups_take_the_form_or_not():
     refused = 0
-    for hq, hkv, _, P, lens, taken in PACKED:
+    for hq, hkv, d, P, lens, taken in PACKED:
         n, ml = len(lens), max(lens)
-        r = _shares(hq, hkv, P, n, ml)
-        assert (r > 0 and _pays(hq, hkv, P, n, ml, sum(lens), r)) == taken, (P, lens)
+        r = _shares(hq, hkv, P, n, ml, d)
+        assert (r > 0 and _pays(hq, hkv, P, n, ml, sum(lens), r, d)) == taken, (P, lens)
         refused += r > 0 and not taken
     assert refused >= 3  # a choice that padded calls make on the device
 
