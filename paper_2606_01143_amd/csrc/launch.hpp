@@ -92,11 +92,12 @@ struct FillRule {
 // The launch's time, in steps per CU: the rounds of shares; suffix tiles in
 // the slots the last round leaves and after it; never less than the longest
 // suffix tile begun after the full rounds, nor than the even spread plus
-// half of it.  Against the even spread it may take 1.25 times that, where the
-// shares are long enough and hardly shorter than that tile; 1.44 times on up to
-// 13 prefix tiles per kv head (2496 keys), 1.5 times at d = 64, where the shared
-// launch is slower by as much, and 1.6 times for suffixes of equal length (all
-// 77 measured gained, 1.02 to 1.8).  Integers only: host and device agree.
+// half of it.  Against the even spread of the useful work it may take 1.25 times
+// that; 1.44 times on up to 13 prefix tiles per kv head (2496 keys), 1.6 times on
+// up to 6 and 1.8 times at d = 64, where the shared launch is slower by as much,
+// and 1.6 times for suffixes of equal length (all 77 measured gained, 1.02 to
+// 1.8).  Shares of fewer than 100 steps do not pay.  Integers only: host and
+// device agree.
 __host__ __device__ inline bool fill_pays(const FillRule& r, long rows) {
   const long steps = r.group * ((rows + 31) / 32), whole = steps / r.shares;
   const long share = (steps + r.shares - 1) / r.shares + kWideTileCost, tiles = r.prefix_tiles * r.shares;
@@ -110,12 +111,12 @@ __host__ __device__ inline bool fill_pays(const FillRule& r, long rows) {
   if (t < after) t = after;
   if (t < spread) t = spread;
   const long useful = r.prefix_tiles * steps + suffix;
-  const long limit = rows == r.n * r.max_len          ? 160
-                     : r.head_dim == 64               ? 150
-                     : r.prefix_tiles <= 13 * r.hkv   ? 144
-                                                      : 125;
-  return useful >= kKvWideMinSteps && whole >= kWideShareSteps && 10 * whole >= 9 * longest &&
-         100 * t * r.slots <= limit * useful;
+  const long limit = rows == r.n * r.max_len        ? 160
+                     : r.head_dim == 64             ? 180
+                     : r.prefix_tiles <= 6 * r.hkv  ? 160
+                     : r.prefix_tiles <= 13 * r.hkv ? 144
+                                                    : 125;
+  return whole >= 100 && 100 * t * r.slots <= limit * useful;
 }
 // where the rows are known on the device only: *out = fill_pays(rule, rows) as
 // 0 or 1, written by the launch that adds up the lengths (null: not asked for)

@@ -300,14 +300,15 @@ SuffixBwdPlan suffix_bwd_base_plan(const spr_dims* d, int32_t n_mb, int32_t max_
 // up to 489: 401 us shared, 408 with the choice), so sizes at which equal
 // lengths do not pay have no R.
 //
-// Suffix backward calls measured, shared launch / this, on 700 packed groups
+// Suffix backward calls measured, shared launch / this, on 1030 packed groups
 // within the 17% (Hq 8-32, Hkv 4 and 8, d 64 and 128, P 500-16000, 2 to 16
 // suffixes of up to 2048, equal, near, drawn, and one long among short): taken
-// wherever equal lengths would be, 0.75 to 1.8 times as fast.  fill_pays takes
-// 544, geometric mean 1.23, five below 0.98 (0.945 at least); the 156 that it
-// leaves hold 91 over 1.05, long prefixes with d = 128, where 0.75 to 1.2 lie
-// close together.  With one limit of 1.25 it took 351 and left gains of 1.1 to
-// 1.8.  Examples in us:
+// wherever equal lengths would be, 0.58 to 1.8 times as fast.  fill_pays, fitted
+// on 700 of them, takes 754, geometric mean 1.23, ten below 0.98 (0.88 at least);
+// the 276 that it leaves average 1.02.  With one limit of 1.25, and only shares
+// hardly shorter than the longest suffix tile, it took less than half and left
+// gains of 1.1 to 1.8.
+// Examples in us:
 //   Hq 32, Hkv 8, d 128, P = 2048, 4 x 1024                  755 ->  669
 //   Hq 32, Hkv 4, d 64,  P = 4255, 10 x 440                 1514 ->  846
 //   Hq 32, Hkv 8, d 128, P = 1143, 13 of 105 to 1991        2237 -> 1272

