@@ -17,7 +17,7 @@
 // 32 x 32 x 2) halve the registers a row or key costs, so a small group
 // still spreads over the chip.  Measured on 32/8 heads, d = 128, P = 1000 and
 // four ragged suffixes, per pass: one thread per row or key on the vector ALU
-// 72.1 ms (0.9 TFLOP/s), this form 1.18 ms (56 TFLOP/s useful; the recompute of
+// 72.1 ms (0.9 TFLOP/s), this form 1.22 ms (54 TFLOP/s useful; the recompute of
 // S and dP for dQ puts 1.3 times that through the matrix cores).
 //
 // v_mfma_f32_16x16x4_f32 operands (lane l, n = l % 16, g = l / 16):
@@ -168,7 +168,7 @@ __device__ __forceinline__ void add_visible(f32x4 (&acc)[D / 16], const float* t
 
 // Query-outer workgroups in one of two forms.  KS = 1: 64 rows of one q
 // head, 16 per wave, every wave takes all 32 keys of a tile.  KS = 2 (launches
-// that cannot give every CU two workgroups of 64 rows): 32 rows, waves 2 and
+// of fewer than 1024 workgroups of 64 rows, four per CU): 32 rows, waves 2 and
 // 3 repeat the rows of waves 0 and 1 and each takes 16 keys of a tile, so a
 // sweep's chain of products is half as long and there are twice the
 // workgroups; the two key halves are merged through LDS at the end.  Measured
@@ -719,7 +719,8 @@ template <int KS>
 long q_blocks(const AttnArgs& a, int n_z) {
   return (long)(QForm<KS>::tiles(a.n_prefix_q_tiles) + QForm<KS>::tiles(a.n_suffix_q_tiles)) * a.hq * n_z;
 }
-// KS = 2 while workgroups of 64 rows cannot give each of the 256 CUs two.
+// KS = 2 below four workgroups of 64 rows per CU; at two (512) it still gains
+// 4% (see QForm).
 constexpr long kF32SplitBelow = 1024;
 }  // namespace
 

@@ -452,7 +452,7 @@ hipError_t launch_bwd(const spr_dims* d, const AttnArgs& a, int n_qz, hipStream_
 struct WsLayout {
   size_t dd_p = 0, dq_acc_p = 0, dd_s = 0, dq_acc_s = 0, dk_acc_p = 0, dv_acc_p = 0;
   size_t lse2_p = 0, lse2_s = 0;
-  size_t part_o = 0, part_lse = 0, part_dq = 0, part_dk = 0, part_dv = 0;
+  size_t part_dq = 0, part_dk = 0, part_dv = 0;
   // padded layout: offsets, clamped lengths, packed copies, inner workspace
   size_t cu = 0, lens_c = 0, pq = 0, pk = 0, pv = 0, po = 0, plse = 0, pdo = 0;
   size_t pdq = 0, pdk = 0, pdv = 0, inner = 0, inner_bytes = 0;
@@ -502,8 +502,9 @@ WsLayout ws_layout(int op, const spr_dims* d, int32_t n_mb, int32_t max_len, int
     return at;
   };
   // both storage types write dQ directly (query-outer role); only the atomic
-  // mode accumulates it in fp32 and converts.  fp32 storage keeps the
-  // accumulator's bytes: Phase C's row shares use them
+  // mode accumulates it in fp32 and converts.  fp32 storage reports the
+  // accumulator's bytes too, as it always has: Phase C's row shares use them,
+  // the suffix backward and the dense baseline leave theirs alone
   const bool f32 = d->dtype == SPR_F32;
   switch (op) {
     case SPR_OP_PREFIX_FWD:
