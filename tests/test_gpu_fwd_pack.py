@@ -1,8 +1,9 @@
 """The suffix forward's packed-row form: the 128 rows of a workgroup are
 consecutive (token, q head) pairs of one kv head, taken where the one-head
 form would need at least 4/3 of the row tiles (short suffixes, or lengths just
-past a multiple of 128).  With few tiles and a prefix, key ranges of the prefix
-are swept for the rows of all suffixes together, the suffixes' own keys apart.
+past a multiple of 128) and is not the faster one.  With few tiles and a
+prefix, key ranges of the prefix are swept for the rows of all suffixes
+together, the suffixes' own keys apart.
 
 O and LSE of every suffix row against the oracle, at one row, tiles that end
 inside a token's heads, suffixes of one and of several tiles, with and without a prefix, split and unsplit, three and eight q
